@@ -113,6 +113,17 @@ __device__ __forceinline__ uint16_t f2bf(float f) {   // round to nearest even
 }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 
+// The exact bfloat16 planes of a float32 value: hi = bf16(w), mid =
+// bf16(w - hi), lo = w - hi - mid (both differences are exact, and lo fits
+// bfloat16's 8 bits).  The bfloat16 arithmetic uses plane 0 only.
+__device__ __forceinline__ void store_planes(uint16_t* dst, int i, int stride, float w, int planes) {
+    for (int p = 0; p < planes; ++p) {
+        const uint16_t b = f2bf(w);
+        dst[p * stride + i] = b;
+        w -= bf2f(b);
+    }
+}
+
 struct PackArgs {
     const float* w1;
     const float* w2;
@@ -139,6 +150,7 @@ struct PackArgs {
 constexpr int kPackThreads = kW2PackF32;
 
 __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
+    const int planes = a.bf16 ? 1 : 3;
     if (gid < kW2PackF32) {
         // float32: index ((mt*16 + q)*64 + lane)*4 + u, step st = 4q + u
         const int u = gid & 3, lane = (gid >> 2) & 63, q = (gid >> 8) & 15, mt = gid >> 12;
@@ -146,13 +158,13 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
         const int row = 32 * mt + m, kk = phi32(st, h);
         a.w2p[gid] = a.w2[row * kH + kk];
         a.w2tp[gid] = a.w2[kk * kH + row];
-        if (a.bf16) {
-            // bfloat16: index ((mt*8 + st)*64 + lane)*8 + i
+        {
+            // bfloat16 planes: index ((mt*8 + st)*64 + lane)*8 + i
             const int i = gid & 7, lane2 = (gid >> 3) & 63, st2 = (gid >> 9) & 7, mt2 = gid >> 12;
             const int m2 = lane2 & 31, h2 = lane2 >> 5;
             const int row2 = 32 * mt2 + m2, k2 = phi16(st2, i, h2);
-            a.w2pb[gid] = f2bf(a.w2[row2 * kH + k2]);
-            a.w2tpb[gid] = f2bf(a.w2[k2 * kH + row2]);
+            store_planes(a.w2pb, gid, kW2PackBF16, a.w2[row2 * kH + k2], planes);
+            if (a.bf16) a.w2tpb[gid] = f2bf(a.w2[k2 * kH + row2]);
         }
     }
     if (gid < 4 * a.w1_q * 64 * 4) {
@@ -177,12 +189,13 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
         const int k = 8 * h + i;
         a.w3tpb[gid] = k < 3 ? f2bf(a.w3[k * kH + 32 * mt + m]) : static_cast<uint16_t>(0);
     }
-    if (a.bf16 && gid < 4 * a.w1_s1 * 64 * 8) {
+    if (gid < 4 * a.w1_s1 * 64 * 8) {
         // bfloat16 layer 1: index ((mt*S1 + st)*64 + lane)*8 + i, k = 16st + 8h + i (< w1_ns)
         const int i = gid & 7, lane = (gid >> 3) & 63, st = (gid >> 9) % a.w1_s1, mt = (gid >> 9) / a.w1_s1;
         const int m = lane & 31, h = lane >> 5;
         const int kk = 16 * st + 8 * h + i;
-        a.w1pb[gid] = kk < a.w1_ns ? f2bf(a.w1[(32 * mt + m) * a.w1_in + kk]) : static_cast<uint16_t>(0);
+        store_planes(a.w1pb, gid, 4 * a.w1_s1 * 64 * 8, kk < a.w1_ns ? a.w1[(32 * mt + m) * a.w1_in + kk] : 0.0f,
+                     planes);
     }
 }
 
@@ -1436,27 +1449,6 @@ __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArg
     if (threadIdx.x < 3)
         out[L::kOffB3 + threadIdx.x] = sRed[threadIdx.x] + sRed[4 + threadIdx.x] + sRed[8 + threadIdx.x] +
                                     sRed[12 + threadIdx.x];
-}
-
-// kx: frequencies of the encoded position in the input (0 or kMaxKX).
-// The bfloat16 forward (under 168 registers) fits three wavefronts per SIMD:
-// three workgroups per compute unit (2 -> 3: 25.7 -> 23.9 us per step at the
-// full configuration); the float32 one, two.
-inline void launch_mlp_fwd(const MlpArgs& a, const PosArgs& pa, int kx, int cus, hipStream_t s) {
-    if (a.bf16 && kx == kMaxKX)
-        DVGO_LAUNCH(K_MLP_FWD, mlp_fwd_bf16_kernel<kMaxKX>, dim3(cus * 3), dim3(256), 0, s, a, pa);
-    else if (a.bf16) DVGO_LAUNCH(K_MLP_FWD, mlp_fwd_bf16_kernel<0>, dim3(cus * 3), dim3(256), 0, s, a, pa);
-    else if (kx == kMaxKX)
-        DVGO_LAUNCH(K_MLP_FWD, mlp_fwd_f32_kernel<kMaxKX>, dim3(cus * 2), dim3(256), 0, s, a, pa);
-    else DVGO_LAUNCH(K_MLP_FWD, mlp_fwd_f32_kernel<0>, dim3(cus * 2), dim3(256), 0, s, a, pa);
-}
-inline void launch_mlp_bwd(const MlpArgs& a, const PosArgs& pa, int kx, int blocks, hipStream_t s) {
-    if (a.bf16 && kx == kMaxKX)
-        DVGO_LAUNCH(K_MLP_BWD, mlp_bwd_bf16_kernel<kMaxKX>, dim3(blocks), dim3(512), 0, s, a, pa);
-    else if (a.bf16) DVGO_LAUNCH(K_MLP_BWD, mlp_bwd_bf16_kernel<0>, dim3(blocks), dim3(512), 0, s, a, pa);
-    else if (kx == kMaxKX)
-        DVGO_LAUNCH(K_MLP_BWD, mlp_bwd_f32_kernel<kMaxKX>, dim3(blocks), dim3(256), 0, s, a, pa);
-    else DVGO_LAUNCH(K_MLP_BWD, mlp_bwd_f32_kernel<0>, dim3(blocks), dim3(256), 0, s, a, pa);
 }
 
 }  // namespace

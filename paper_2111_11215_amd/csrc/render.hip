@@ -20,6 +20,7 @@
 #include "adam.hpp"
 #include "common.hpp"
 #include "mlp_mfma.hpp"
+#include "mlp_split.hpp"
 #include "scan.hpp"
 
 using dvgo::GridArgs;
@@ -49,8 +50,8 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.w1p = take(kW1PackF32Max * 4);
     L.w2p = take(kW2PackF32 * 4);
     L.w2tp = take(kW2PackF32 * 4);
-    L.w1pb = take(kW1PackBF16Max * 2);
-    L.w2pb = take(kW2PackBF16 * 2);
+    L.w1pb = take(3 * kW1PackBF16Max * 2);   // the three planes of the float32 form
+    L.w2pb = take(3 * kW2PackBF16 * 2);
     L.w2tpb = take(kW2PackBF16 * 2);
     L.w3pb = take(kW3PackBF16 * 2);
     L.w3tpb = take(kW3TPackBF16 * 2);

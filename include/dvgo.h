@@ -74,8 +74,9 @@ typedef struct dvgo_field {
 /* The shallow colour network of Eq. fine_queries: input [feat(C), PE(d)(27)],
  * two ReLU layers of `hidden` (must be 128) and a sigmoid RGB output.
  * Weights are float32 masters [out][in]; `precision` selects the arithmetic
- * of its matrix products: DVGO_F32 (float32 matrix cores) or DVGO_BF16
- * (bfloat16 inputs, float32 accumulation).
+ * of its matrix products: DVGO_F32 (float32 values, each the exact sum of
+ * three bfloat16 ones on the matrix cores) or DVGO_BF16 (bfloat16 inputs);
+ * float32 accumulation.
  * pe_x = 5 selects the paper's network that also takes the encoded query
  * position (Eq. fine_queries with k_x = 5 frequencies, supplementary
  * implementation details): input [feat(C), PE_5(u)(33), PE(d)(27)] (72 for

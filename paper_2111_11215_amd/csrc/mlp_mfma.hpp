@@ -1,8 +1,9 @@
 // Colour network of the fine stage (paper Eq. fine_queries: two ReLU layers
-// of 128 and a sigmoid RGB head) on CDNA4 matrix cores.
+// of 128 and a sigmoid RGB head) on CDNA4 matrix cores: the operand packing
+// of both forms and the bfloat16 form (the float32 one is in mlp_split.hpp).
 //
-// Layout.  A 32x32 accumulator tile of v_mfma_f32_32x32x{2f32,16bf16} holds,
-// in lane l and register r, row 8*(r/4) + 4*(l/32) + (r%4) and column l%32.
+// Layout.  A 32x32 accumulator tile of v_mfma_f32_32x32x16_bf16 holds, in
+// lane l and register r, row 8*(r/4) + 4*(l/32) + (r%4) and column l%32.
 // Activations are kept transposed ("feature rows, sample columns"): a wave
 // owns 32 samples (one per lane column) and each lane holds 16 features per
 // 32-feature tile.  The next layer consumes those registers directly as its
@@ -44,7 +45,7 @@ constexpr int kW1TPackBF16 = 8 * 64 * 8;   // W1[:, :12]^T as a 32-row tile (row
 // PE_KX(u) (3 + 6 KX), PE(d) (27)], u the position in box coordinates.  The
 // per-sample part of the first layer is [feat, PE_KX(u)] (kS values); the
 // view part is evaluated once per ray as before.  KX = 0 is the 39-input
-// network above.  Float32 matrix cores only.
+// network above.
 template <int KX>
 struct NetLayout {
     static constexpr int kXPE = KX ? 3 + 6 * KX : 0;
@@ -74,9 +75,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ f32x16 mma_f32(float a, float b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ f32x16 mma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -98,7 +96,7 @@ __device__ __forceinline__ T* opaque(T* p) {
 
 // Row within a 32-row accumulator tile of register r in lane half h.
 __host__ __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
-// Feature consumed at float32 chain step st (0..63) by lane half h.
+// Feature at step st (0..63), half h of the plain float32 chain's input order.
 __host__ __device__ __forceinline__ int phi32(int st, int h) { return 32 * (st >> 4) + acc_row(st & 15, h); }
 // Feature consumed at bfloat16 chain step st (0..7), element i (0..7), half h.
 __host__ __device__ __forceinline__ int phi16(int st, int i, int h) {
@@ -133,7 +131,6 @@ struct PackArgs {
     uint16_t* w1tpb;
     float* w1p;
     float* w2p;
-    float* w2tp;
     uint16_t* w1pb;
     uint16_t* w2pb;
     uint16_t* w2tpb;
@@ -157,14 +154,13 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
         const int st = 4 * q + u, m = lane & 31, h = lane >> 5;
         const int row = 32 * mt + m, kk = phi32(st, h);
         a.w2p[gid] = a.w2[row * kH + kk];
-        a.w2tp[gid] = a.w2[kk * kH + row];
         {
             // bfloat16 planes: index ((mt*8 + st)*64 + lane)*8 + i
             const int i = gid & 7, lane2 = (gid >> 3) & 63, st2 = (gid >> 9) & 7, mt2 = gid >> 12;
             const int m2 = lane2 & 31, h2 = lane2 >> 5;
             const int row2 = 32 * mt2 + m2, k2 = phi16(st2, i, h2);
             store_planes(a.w2pb, gid, kW2PackBF16, a.w2[row2 * kH + k2], planes);
-            if (a.bf16) a.w2tpb[gid] = f2bf(a.w2[k2 * kH + row2]);
+            store_planes(a.w2tpb, gid, kW2PackBF16, a.w2[k2 * kH + row2], planes);
         }
     }
     if (gid < 4 * a.w1_q * 64 * 4) {
@@ -174,13 +170,13 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
         const int kk = 2 * st + h;
         a.w1p[gid] = kk < a.w1_ns ? a.w1[(32 * mt + m) * a.w1_in + kk] : 0.0f;
     }
-    if (a.bf16 && gid < kW3PackBF16) {
+    if (gid < kW3PackBF16) {
         // index (st*64 + lane)*8 + i; lane (m, h), element i
         const int i = gid & 7, lane = (gid >> 3) & 63, st = gid >> 9;
         const int m = lane & 31, h = lane >> 5;
         const int k = phi16(st, i, h);
         a.w3pb[gid] = m < 3 ? f2bf(a.w3[m * kH + k]) : static_cast<uint16_t>(0);
-        a.w1tpb[gid] = m < kC ? f2bf(a.w1[k * a.w1_in + m]) : static_cast<uint16_t>(0);
+        store_planes(a.w1tpb, gid, kW1TPackBF16, m < kC ? a.w1[k * a.w1_in + m] : 0.0f, planes);
     }
     if (a.bf16 && gid < kW3TPackBF16) {
         // index (mt*64 + lane)*8 + i, k = 8h + i (< 3)
@@ -212,7 +208,6 @@ struct MlpArgs {
     const float* pe;      // [B][32]
     const float* w1p;
     const float* w2p;
-    const float* w2tp;
     const uint16_t* w1pb;
     const uint16_t* w2pb;
     const uint16_t* w2tpb;
@@ -229,6 +224,7 @@ struct MlpArgs {
     const float4* rec_head;   // [cap] (fx, fy, fz, dL/draw)
     float4* rec;              // [cap][4] binned records
     int nrays;                // rows of base and pe
+    uint32_t* live;           // [cap][8] ReLU branches (float32 form; NULL: not wanted)
 };
 
 // The query position of each sample, for the networks with an encoded
@@ -259,7 +255,6 @@ __device__ __forceinline__ MlpArgs refresh(const MlpArgs& a) {
     l.b3 = opaque(a.b3);
     l.w1p = opaque(a.w1p);
     l.w2p = opaque(a.w2p);
-    l.w2tp = opaque(a.w2tp);
     l.w1pb = opaque(a.w1pb);
     l.w2pb = opaque(a.w2pb);
     l.w2tpb = opaque(a.w2tpb);
@@ -268,14 +263,6 @@ __device__ __forceinline__ MlpArgs refresh(const MlpArgs& a) {
     l.w1tpb = opaque(a.w1tpb);
     return l;
 }
-
-// ---------------------------------------------------------------------------
-// forward chain for the 32 samples of one wave (float32 matrix cores)
-// ---------------------------------------------------------------------------
-struct ChainF32 {
-    f32x16 h1[4];   // relu(layer-1) per 32-feature tile
-    f32x16 z2[4];   // layer-2 pre-activation
-};
 
 __device__ __forceinline__ void load_base(const float* base, int r, int h, f32x16 acc[4]) {
     const float* br = base + static_cast<int64_t>(r) * kH;
@@ -289,80 +276,6 @@ __device__ __forceinline__ void load_base(const float* base, int r, int h, f32x1
             acc[mt][4 * q + 2] = v.z;
             acc[mt][4 * q + 3] = v.w;
         }
-}
-
-// One chained 128x128 layer: out[mt] += W * in, one output tile at a time
-// (dependent matrix-core ops accumulate back to back).  Packed operands are
-// read from `w2op` (LDS or global memory), one float4 per 4 steps.
-template <typename P>
-__device__ __forceinline__ f32x16 chain_tile_f32(const P* w2op, int lane, int mt, const f32x16 in[4], f32x16 acc) {
-    #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const float4 a4 = w2op[(mt * 16 + q) * 64 + lane];
-        #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int st = 4 * q + u;
-            acc = mma_f32(a4[u], in[st >> 4][st & 15], acc);
-        }
-    }
-    return acc;
-}
-
-// Layer 1 on the per-sample inputs xs (kS values: features, then the
-// encoded position), then layer 2.  Lane half h supplies input 2 st + h of
-// step st.
-template <int KX, typename P>
-__device__ __forceinline__ void forward_chain_f32(const MlpArgs& a, const P* w2op, int r,
-                                                  const float xs[NetLayout<KX>::kS], int lane, ChainF32& c) {
-    using L = NetLayout<KX>;
-    const int h = lane >> 5;
-    load_base(a.base, r, h, c.h1);
-    const float4* w1p = reinterpret_cast<const float4*>(a.w1p);
-    #pragma unroll
-    for (int q = 0; q < L::kQ1; ++q) {
-        float4 a4[4];
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) a4[mt] = w1p[(mt * L::kQ1 + q) * 64 + lane];
-        #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k0 = 2 * (4 * q + u), k1 = k0 + 1;   // compile-time indices
-            const float v0 = k0 < L::kS ? xs[k0 < L::kS ? k0 : 0] : 0.0f;
-            const float v1 = k1 < L::kS ? xs[k1 < L::kS ? k1 : 0] : 0.0f;
-            const float b = h ? v1 : v0;
-            #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) c.h1[mt] = mma_f32(a4[mt][u], b, c.h1[mt]);
-        }
-    }
-    #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            c.h1[mt][rr] = fmaxf(c.h1[mt][rr], 0.0f);
-            c.z2[mt][rr] = a.b2[32 * mt + acc_row(rr, h)];
-        }
-    #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) c.z2[mt] = chain_tile_f32(w2op, lane, mt, c.h1, c.z2[mt]);
-}
-
-// Layer 3 and the sigmoid: both lane halves end with the sample's colour.
-__device__ __forceinline__ void head(const MlpArgs& a, const f32x16 z2[4], int h, float c[3]) {
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-    #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            const int j = 32 * mt + acc_row(rr, h);
-            const float hv = fmaxf(z2[mt][rr], 0.0f);
-            s0 += a.w3[j] * hv;
-            s1 += a.w3[kH + j] * hv;
-            s2 += a.w3[2 * kH + j] * hv;
-        }
-    s0 += __shfl_xor(s0, 32, 64);
-    s1 += __shfl_xor(s1, 32, 64);
-    s2 += __shfl_xor(s2, 32, 64);
-    c[0] = 1.0f / (1.0f + expf(-(s0 + a.b3[0])));
-    c[1] = 1.0f / (1.0f + expf(-(s1 + a.b3[1])));
-    c[2] = 1.0f / (1.0f + expf(-(s2 + a.b3[2])));
 }
 
 __device__ __forceinline__ void load_feat(const float* feat, int64_t s, float f[12]) {
@@ -430,258 +343,9 @@ __device__ __forceinline__ void sample_inputs(const PosArgs& a, const float* fea
     sample_encode<KX>(a, in, xs);
 }
 
-// Forward: colour of every listed sample.  LDS holds the packed W2.
-template <int KX>
-__global__ __launch_bounds__(256, 2) void mlp_fwd_f32_kernel(MlpArgs a0, PosArgs pa) {
-    const MlpArgs& a = a0;
-    __shared__ float4 sW2[kW2PackF32 / 4];
-    for (int i = threadIdx.x; i < kW2PackF32 / 4; i += blockDim.x)
-        sW2[i] = reinterpret_cast<const float4*>(a.w2p)[i];
-    __syncthreads();
-    const int64_t n = *a.n_kept < a.cap ? *a.n_kept : a.cap;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 31, h = lane >> 5;
-    for (int64_t tile = static_cast<int64_t>(blockIdx.x) * 4 + wave; tile * 32 < n;
-         tile += static_cast<int64_t>(gridDim.x) * 4) {
-        const MlpArgs a = refresh(a0);
-        const int64_t s = tile * 32 + m;
-        const bool ok = s < n;
-        const int64_t sc = ok ? s : n - 1;
-        const int r = a.sample_ray[sc];
-        float xs[NetLayout<KX>::kS];
-        sample_inputs<KX>(pa, a.feat, sc, r, xs);
-        ChainF32 c;
-        forward_chain_f32<KX>(a, sW2, r, xs, lane, c);
-        float col[3];
-        head(a, c.z2, h, col);
-        if (ok && h == 0) reinterpret_cast<float4*>(a.col)[s] = make_float4(col[0], col[1], col[2], 0.0f);
-    }
-}
-
 // ---------------------------------------------------------------------------
-// backward (float32): recompute, adjoint chain, weight gradients
-// ---------------------------------------------------------------------------
-constexpr int kSRow = 132;      // LDS row pitch (floats) of a staged sample row
-
-template <int KX>
-__global__ __launch_bounds__(256, 1) void mlp_bwd_f32_kernel(MlpArgs a0, PosArgs pa) {
-    using L = NetLayout<KX>;
-    __shared__ float sA[128 * kSRow];   // h1 rows, then dL/dz1 rows
-    __shared__ float sB[128 * kSRow];   // h2 / dL/dz2 rows, then x' = [f, PE, 1, 0..] rows
-    const int64_t n = *a0.n_kept < a0.cap ? *a0.n_kept : a0.cap;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 31, h = lane >> 5;
-    f32x16 dW2[4], dW1[L::kXT];
-    #pragma unroll
-    for (int t = 0; t < 4; ++t)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) dW2[t][rr] = 0.0f;
-    #pragma unroll
-    for (int t = 0; t < L::kXT; ++t)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) dW1[t][rr] = 0.0f;
-    float dW3a[3] = {0, 0, 0}, dW3b[3] = {0, 0, 0}, db2a = 0.0f, db2b = 0.0f, db3[3] = {0, 0, 0};
-    float* myA = sA + wave * 32 * kSRow;
-    float* myB = sB + wave * 32 * kSRow;
-    for (int64_t blk = blockIdx.x; blk * 128 < n; blk += gridDim.x) {
-        const MlpArgs a = refresh(a0);
-        const float4* w2p = reinterpret_cast<const float4*>(a.w2p);
-        const float4* w2tp = reinterpret_cast<const float4*>(a.w2tp);
-        const int64_t s = blk * 128 + wave * 32 + m;
-        const bool ok = s < n;
-        const int64_t sc = ok ? s : n - 1;
-        const int r = a.sample_ray[sc];
-        float xs[L::kS];
-        sample_inputs<KX>(pa, a.feat, sc, r, xs);
-        ChainF32 c;
-        forward_chain_f32<KX>(a, w2p, r, xs, lane, c);
-        float col[3];
-        head(a, c.z2, h, col);
-        float dz3[3] = {0, 0, 0};
-        if (ok) {
-            const float4 dc = reinterpret_cast<const float4*>(a.col)[s];
-            dz3[0] = dc.x * col[0] * (1.0f - col[0]);
-            dz3[1] = dc.y * col[1] * (1.0f - col[1]);
-            dz3[2] = dc.z * col[2] * (1.0f - col[2]);
-        }
-        // ---- dW3, db3 from h2 rows and dz3 staged in LDS
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(myA + m * kSRow + 32 * mt + 8 * q + 4 * h) =
-                    make_float4(fmaxf(c.z2[mt][4 * q], 0.0f), fmaxf(c.z2[mt][4 * q + 1], 0.0f),
-                                fmaxf(c.z2[mt][4 * q + 2], 0.0f), fmaxf(c.z2[mt][4 * q + 3], 0.0f));
-        if (h == 0) {
-            myB[m * kSRow + 0] = dz3[0];
-            myB[m * kSRow + 1] = dz3[1];
-            myB[m * kSRow + 2] = dz3[2];
-            db3[0] += dz3[0];
-            db3[1] += dz3[1];
-            db3[2] += dz3[2];
-        }
-        __syncthreads();
-        #pragma unroll 4
-        for (int ss = 0; ss < 32; ++ss) {
-            const float ha = myA[ss * kSRow + lane], hb = myA[ss * kSRow + lane + 64];
-            const float d0 = myB[ss * kSRow], d1 = myB[ss * kSRow + 1], d2 = myB[ss * kSRow + 2];
-            dW3a[0] += d0 * ha; dW3a[1] += d1 * ha; dW3a[2] += d2 * ha;
-            dW3b[0] += d0 * hb; dW3b[1] += d1 * hb; dW3b[2] += d2 * hb;
-        }
-        __syncthreads();
-        // ---- dz2 = (W3^T dz3) * relu'(z2), in place of z2
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            #pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int j = 32 * mt + acc_row(rr, h);
-                const float dh = a.w3[j] * dz3[0] + a.w3[kH + j] * dz3[1] + a.w3[2 * kH + j] * dz3[2];
-                c.z2[mt][rr] = c.z2[mt][rr] > 0.0f ? dh : 0.0f;
-            }
-        // ---- stage h1 rows (sA) and dz2 rows (sB) of all four waves
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                *reinterpret_cast<float4*>(myA + m * kSRow + 32 * mt + 8 * q + 4 * h) =
-                    make_float4(c.h1[mt][4 * q], c.h1[mt][4 * q + 1], c.h1[mt][4 * q + 2], c.h1[mt][4 * q + 3]);
-                *reinterpret_cast<float4*>(myB + m * kSRow + 32 * mt + 8 * q + 4 * h) =
-                    make_float4(c.z2[mt][4 * q], c.z2[mt][4 * q + 1], c.z2[mt][4 * q + 2], c.z2[mt][4 * q + 3]);
-            }
-        __syncthreads();
-        #pragma unroll 4
-        for (int ss = 0; ss < 32; ++ss) {
-            db2a += myB[ss * kSRow + lane];
-            db2b += myB[ss * kSRow + lane + 64];
-        }
-        // dW2[j in tile `wave`][i] += sum over the 128 staged samples
-        #pragma unroll 1
-        for (int src = 0; src < 4; ++src)
-            #pragma unroll 4
-            for (int st = 0; st < 16; ++st) {
-                const int row = src * 32 + 2 * st + h;
-                const float av = sB[row * kSRow + 32 * wave + m];
-                #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) dW2[nt] = mma_f32(av, sA[row * kSRow + 32 * nt + m], dW2[nt]);
-            }
-        // ---- dh1 = W2^T dz2 (chained), dz1 = dh1 * relu'(h1), in place of h1
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            f32x16 dh1;
-            #pragma unroll
-            for (int rr = 0; rr < 16; ++rr) dh1[rr] = 0.0f;
-            dh1 = chain_tile_f32(w2tp, lane, mt, c.z2, dh1);
-            #pragma unroll
-            for (int rr = 0; rr < 16; ++rr) c.h1[mt][rr] = c.h1[mt][rr] > 0.0f ? dh1[rr] : 0.0f;
-        }
-        // ---- dL/dfeat = W1[:, :12]^T dz1
-        float df[12];
-        #pragma unroll
-        for (int cc = 0; cc < 12; ++cc) df[cc] = 0.0f;
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            #pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int i = 32 * mt + acc_row(rr, h);
-                const float d = c.h1[mt][rr];
-                #pragma unroll
-                for (int cc = 0; cc < 12; ++cc) df[cc] += a.w1[i * L::kIn + cc] * d;
-            }
-        #pragma unroll
-        for (int cc = 0; cc < 12; ++cc) df[cc] += __shfl_xor(df[cc], 32, 64);
-        __syncthreads();
-        // ---- stage dz1 rows (sA) and x' rows (sB)
-        #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(myA + m * kSRow + 32 * mt + 8 * q + 4 * h) =
-                    make_float4(c.h1[mt][4 * q], c.h1[mt][4 * q + 1], c.h1[mt][4 * q + 2], c.h1[mt][4 * q + 3]);
-        {
-            // x' = [per-sample inputs, PE(d), 1, 0...]: lane half h stages
-            // columns kHalf h .. kHalf h + kHalf - 1 (both candidates of a
-            // column are compile-time indices)
-            constexpr int kHalf = 16 * L::kXT;
-            const float* per = a.pe + static_cast<int64_t>(r) * 32;
-            float* row = myB + m * kSRow + kHalf * h;
-            auto xval = [&](int j) -> float {
-                if (j < L::kS) return xs[j < L::kS ? j : 0];
-                if (j < L::kIn) return per[j - L::kS];
-                return j == L::kIn ? 1.0f : 0.0f;
-            };
-            #pragma unroll
-            for (int cc = 0; cc < kHalf; ++cc) row[cc] = h ? xval(kHalf + cc) : xval(cc);
-        }
-        if (ok && h == 0) {
-            float4* rec = binned_record(a, s);
-            rec[0] = a.rec_head[s];
-            rec[1] = make_float4(df[0], df[1], df[2], df[3]);
-            rec[2] = make_float4(df[4], df[5], df[6], df[7]);
-            rec[3] = make_float4(df[8], df[9], df[10], df[11]);
-        }
-        __syncthreads();
-        // dW1[i in tile `wave`][col] (col 39 = bias) over the 128 staged samples
-        #pragma unroll 1
-        for (int src = 0; src < 4; ++src)
-            #pragma unroll 4
-            for (int st = 0; st < 16; ++st) {
-                const int row = src * 32 + 2 * st + h;
-                const float av = sA[row * kSRow + 32 * wave + m];
-                #pragma unroll
-                for (int nt = 0; nt < L::kXT; ++nt) dW1[nt] = mma_f32(av, sB[row * kSRow + 32 * nt + m], dW1[nt]);
-            }
-        __syncthreads();
-    }
-    // ---- epilogue: this workgroup's partial of the flat gradient
-    float* out = a0.partial + static_cast<int64_t>(blockIdx.x) * L::kPStride;
-    #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            const int j = 32 * wave + acc_row(rr, h);
-            out[L::kOffW2 + j * kH + 32 * nt + m] = dW2[nt][rr];
-        }
-    #pragma unroll
-    for (int nt = 0; nt < L::kXT; ++nt)
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            const int i = 32 * wave + acc_row(rr, h);
-            const int col = 32 * nt + m;
-            if (col < L::kIn) out[L::kOffW1 + i * L::kIn + col] = dW1[nt][rr];
-            else if (col == L::kIn) out[L::kOffB1 + i] = dW1[nt][rr];
-        }
-    #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        db3[t] += __shfl_xor(db3[t], 32, 64);
-        #pragma unroll
-        for (int off = 16; off > 0; off >>= 1) db3[t] += __shfl_xor(db3[t], off, 64);
-    }
-    float* red = sA;   // [4 waves][512]
-    #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        red[wave * 512 + t * kH + lane] = dW3a[t];
-        red[wave * 512 + t * kH + lane + 64] = dW3b[t];
-    }
-    red[wave * 512 + 384 + lane] = db2a;
-    red[wave * 512 + 384 + lane + 64] = db2b;
-    if (lane == 0)
-        #pragma unroll
-        for (int t = 0; t < 3; ++t) sB[wave * 4 + t] = db3[t];
-    __syncthreads();
-    for (int i = threadIdx.x; i < 512; i += blockDim.x) {
-        const float v = red[i] + red[512 + i] + red[1024 + i] + red[1536 + i];
-        if (i < 384) out[L::kOffW3 + i] = v;
-        else out[L::kOffB2 + (i - 384)] = v;
-    }
-    if (threadIdx.x < 3) out[L::kOffB3 + threadIdx.x] = sB[threadIdx.x] + sB[4 + threadIdx.x] + sB[8 + threadIdx.x] +
-                                                   sB[12 + threadIdx.x];
-}
-
-// ---------------------------------------------------------------------------
-// bfloat16 matrix cores (v_mfma_f32_32x32x16_bf16): same dataflow, K = 16
-// per step, 8 consecutive K values per lane half; float32 accumulation.
-// Weight-gradient operands are staged as [feature][sample] bfloat16 so that
-// a lane's 8 consecutive samples are one 16-byte LDS read.
+// bfloat16 matrix cores (v_mfma_f32_32x32x16_bf16): K = 16 per step, 8
+// consecutive K values per lane half; float32 accumulation.
 // ---------------------------------------------------------------------------
 constexpr int kBP = 136;   // LDS pitch (bf16 elements) of a staged feature row
 constexpr int kTP = 128;   // LDS pitch (bf16) of a staged sample row [sample][feature]

@@ -31,8 +31,8 @@ namespace {
 constexpr int kMaxBwdBlocks = 256;
 
 struct WsLayout {
-    size_t base, pe, w1p, w2p, w2tp, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
-        cell_start, scan_tmp, cell_rank, rec_head, rec, step_rgb, step_grad, step_logt, step_sqerr, total;
+    size_t base, pe, w1p, w2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
+        cell_start, scan_tmp, cell_rank, rec_head, rec, live, step_rgb, step_grad, step_logt, step_sqerr, total;
 };
 
 constexpr int kScanPer = 8192;   // elements per block of the device-wide scan
@@ -49,13 +49,12 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.pe = take(static_cast<size_t>(B) * 32 * 4);
     L.w1p = take(kW1PackF32Max * 4);
     L.w2p = take(kW2PackF32 * 4);
-    L.w2tp = take(kW2PackF32 * 4);
     L.w1pb = take(3 * kW1PackBF16Max * 2);   // the three planes of the float32 form
     L.w2pb = take(3 * kW2PackBF16 * 2);
-    L.w2tpb = take(kW2PackBF16 * 2);
+    L.w2tpb = take(3 * kW2PackBF16 * 2);
     L.w3pb = take(kW3PackBF16 * 2);
     L.w3tpb = take(kW3TPackBF16 * 2);
-    L.w1tpb = take(kW1TPackBF16 * 2);
+    L.w1tpb = take(3 * kW1TPackBF16 * 2);
     L.raw = take(static_cast<size_t>(cap) * 4);
     L.feat = take(static_cast<size_t>(cap) * kC * 4);
     L.col = take(static_cast<size_t>(cap) * 4 * 4);
@@ -66,6 +65,7 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.cell_rank = take(static_cast<size_t>(cap) * 8);
     L.rec_head = take(static_cast<size_t>(cap) * 16);
     L.rec = take(static_cast<size_t>(cap) * 64);
+    L.live = take(static_cast<size_t>(cap) * 32);         // ReLU branches (float32 form)
     L.step_rgb = take(static_cast<size_t>(B) * 3 * 4);    // per-ray state of dvgo_train_step
     L.step_grad = take(static_cast<size_t>(B) * 3 * 4);
     L.step_logt = take(static_cast<size_t>(B) * 4);
@@ -1277,7 +1277,6 @@ PrepArgs prep_args(const Common& cm, const dvgo_mlp* mlp, int* zero, int64_t nze
         pk.w2 = mlp->w2;
         pk.w1p = reinterpret_cast<float*>(cm.ws + cm.L.w1p);
         pk.w2p = reinterpret_cast<float*>(cm.ws + cm.L.w2p);
-        pk.w2tp = reinterpret_cast<float*>(cm.ws + cm.L.w2tp);
         pk.w1pb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w1pb);
         pk.w2pb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w2pb);
         pk.w2tpb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w2tpb);
@@ -1365,7 +1364,7 @@ int32_t run_prep_gather(const Common& cm, const dvgo_mlp* mlp, const dvgo_field*
     return dvgo::launch_status();
 }
 
-MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_kept) {
+MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_kept, bool training) {
     MlpArgs ma;
     ma.nrays = cm.B;
     ma.sample_ray = cm.sa.sample_ray;
@@ -1379,7 +1378,6 @@ MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_ke
     ma.pe = reinterpret_cast<const float*>(cm.ws + cm.L.pe);
     ma.w1p = reinterpret_cast<const float*>(cm.ws + cm.L.w1p);
     ma.w2p = reinterpret_cast<const float*>(cm.ws + cm.L.w2p);
-    ma.w2tp = reinterpret_cast<const float*>(cm.ws + cm.L.w2tp);
     ma.w1pb = reinterpret_cast<const uint16_t*>(cm.ws + cm.L.w1pb);
     ma.w2pb = reinterpret_cast<const uint16_t*>(cm.ws + cm.L.w2pb);
     ma.w2tpb = reinterpret_cast<const uint16_t*>(cm.ws + cm.L.w2tpb);
@@ -1390,6 +1388,7 @@ MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_ke
     ma.col = reinterpret_cast<float*>(cm.ws + cm.L.col);
     ma.partial = reinterpret_cast<float*>(cm.ws + cm.L.partial);
     ma.bf16 = mlp->precision == DVGO_BF16;
+    ma.live = training && !ma.bf16 ? reinterpret_cast<uint32_t*>(cm.ws + cm.L.live) : nullptr;
     return ma;
 }
 
@@ -1555,7 +1554,7 @@ int32_t render_bwd_impl(const dvgo_field* field, const dvgo_mlp* mlp, const floa
                             workspace);
     const Bins bins = bins_of(cm, field);
     MlpArgs ma;
-    if (mlp) ma = make_mlp_args(cm, mlp, n_kept);
+    if (mlp) ma = make_mlp_args(cm, mlp, n_kept, true);
     if (!forward_done) {
         // prep (packing, per-ray encoding) also clears the cell counts
         if (int32_t st = run_prep_gather(cm, mlp, field, n_kept, s, bins.cell_count, bins.ncell + 1)) return st;
@@ -1663,7 +1662,7 @@ int32_t dvgo_render_fwd(const dvgo_field* field, const dvgo_mlp* mlp, const floa
         if (int32_t st = run_prep_gather(cm, mlp, field, n_kept, s)) return st;
     }
     if (mlp && capacity > 0) {
-        MlpArgs ma = make_mlp_args(cm, mlp, n_kept);
+        MlpArgs ma = make_mlp_args(cm, mlp, n_kept, false);
         launch_mlp_fwd(ma, make_pos_args(cm), mlp->pe_x, dvgo::device_cu_count(), s);
         if (int32_t st = dvgo::launch_status()) return st;
     }
@@ -1779,7 +1778,7 @@ int32_t dvgo_train_step(const dvgo_field* field, const dvgo_mlp* mlp, const floa
                             workspace);
     const Bins bins = bins_of(cm, field);
     if (int32_t st = run_prep_gather(cm, mlp, field, n_kept, s, bins.cell_count, bins.ncell + 1)) return st;
-    MlpArgs ma = make_mlp_args(cm, mlp, n_kept);
+    MlpArgs ma = make_mlp_args(cm, mlp, n_kept, true);
     launch_mlp_fwd(ma, make_pos_args(cm), mlp->pe_x, dvgo::device_cu_count(), s);
     if (int32_t st = dvgo::launch_status()) return st;
     float* sq_w = reinterpret_cast<float*>(ws + L.step_sqerr);

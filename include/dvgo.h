@@ -529,10 +529,14 @@ int32_t dvgo_proposal_bwd_adam(const float* rays_o, const float* rays_d, const f
  * are held fixed (it supervises the colours only); H's gradient is zero
  * where the clamp is active.  target [B][3]; rgb [B][3] (or NULL) receives
  * C_r; loss (device float) L; grad_density [n] and grad_rgb [n][3] are
- * ACCUMULATED (+=) with float atomics (the summation order varies between
- * runs).  The adjoint walks each ray from its end with the transmittance
- * recomputed by prefix sums.  max_samples (the sampler's) at most 4096, else
- * DVGO_E_UNSUPPORTED.  workspace: dvgo_coarse_workspace_bytes(B). */
+ * ACCUMULATED (+=; the summation order varies between runs).  The adjoint
+ * walks each ray from its end with the transmittance recomputed by prefix
+ * sums.  max_samples (the sampler's) at most 4096, else DVGO_E_UNSUPPORTED.
+ * workspace: at least dvgo_coarse_workspace_bytes(B); with the larger
+ * dvgo_coarse_step_workspace_bytes(B, capacity, &field.box) (0 for an invalid
+ * box), 16-byte aligned, the samples are sorted by cell and each vertex
+ * gathers its gradient, without it they are scattered with float atomics,
+ * several times slower. */
 typedef struct dvgo_coarse_field {
     const float* density;
     const float* rgb;
@@ -540,6 +544,7 @@ typedef struct dvgo_coarse_field {
     float act_shift;
 } dvgo_coarse_field;
 size_t dvgo_coarse_workspace_bytes(int32_t B);
+size_t dvgo_coarse_step_workspace_bytes(int32_t B, int64_t capacity, const dvgo_box* grid /*host*/);
 int32_t dvgo_coarse_step(const dvgo_coarse_field* field /*host*/, const float* rays_o, const float* rays_d,
                          const float* jitter, const float* t_near, const int32_t* perm, const int32_t* ray_offset,
                          const int32_t* sample_k, const int64_t* n_kept, int64_t capacity, int32_t B,

@@ -115,6 +115,7 @@ SIGNATURES = {
                                     POINTER(FineFilter), POINTER(c_float), c_int32, P, P, P, P, P, P, c_size_t, P]),
     "dvgo_grid_resample": (c_int32, [P, POINTER(Box), c_int32, P, POINTER(Box), P]),
     "dvgo_coarse_workspace_bytes": (c_size_t, [c_int32]),
+    "dvgo_coarse_step_workspace_bytes": (c_size_t, [c_int32, c_int64, POINTER(Box)]),
     "dvgo_coarse_step": (c_int32, [POINTER(CoarseField), P, P, P, P, P, P, P, P, c_int64, c_int32, c_int32, c_float,
                                    POINTER(c_float), P, c_float, c_float, P, P, P, P, P, c_size_t, P]),
     "dvgo_view_counts_workspace_bytes": (c_size_t, []),

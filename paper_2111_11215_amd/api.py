@@ -600,7 +600,7 @@ def coarse_step(density: torch.Tensor, rgb_grid: torch.Tensor, box_min, box_max,
                          float(act_shift))
     rgb = torch.empty((s.B, 3), dtype=torch.float32, device=dev) if want_rgb else None
     loss = torch.empty(1, dtype=torch.float32, device=dev)
-    nws = lib.dvgo_coarse_workspace_bytes(s.B)
+    nws = lib.dvgo_coarse_step_workspace_bytes(s.B, s.capacity, ctypes.byref(f.box))
     ws = workspace(nws, dev)
     check("dvgo_coarse_step", lib.dvgo_coarse_step(
         ctypes.byref(f), _ptr(s.rays_o), _ptr(s.rays_d), _ptr(s.jitter), _ptr(s.t_near), _ptr(s.perm),

@@ -18,6 +18,7 @@
 //            float atomics), the grids' Adam step fused in
 //   reduce   deterministic sum of the per-block weight-gradient partials
 #include "adam.hpp"
+#include "binning.hpp"
 #include "common.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_split.hpp"
@@ -34,8 +35,6 @@ struct WsLayout {
     size_t base, pe, w1p, w2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
         cell_start, scan_tmp, cell_rank, rec_head, rec, live, step_rgb, step_grad, step_logt, step_sqerr, total;
 };
-
-constexpr int kScanPer = 8192;   // elements per block of the device-wide scan
 
 WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     WsLayout L;
@@ -61,7 +60,7 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.partial = take(static_cast<size_t>(kMaxBwdBlocks) * kPStrideMax * 4);
     L.cell_count = take(static_cast<size_t>(ncell + 1) * 4);
     L.cell_start = take(static_cast<size_t>(ncell + 1) * 4);
-    L.scan_tmp = take(static_cast<size_t>((ncell + 1 + kScanPer - 1) / kScanPer + 1) * 8);
+    L.scan_tmp = take(cell_scan_bytes(ncell + 1));
     L.cell_rank = take(static_cast<size_t>(cap) * 8);
     L.rec_head = take(static_cast<size_t>(cap) * 16);
     L.rec = take(static_cast<size_t>(cap) * 64);
@@ -384,26 +383,6 @@ __device__ __forceinline__ int cell_of(const GridArgs& g, const float x[3], floa
     return (i0[0] * (g.n[1] - 1) + i0[1]) * (g.n[2] - 1) + i0[2];
 }
 
-// Rank of this lane's sample among the samples of its cell.  Lanes hold
-// consecutive samples, so equal cells form runs; each run's first lane adds
-// the run length to the cell's count with one atomic, and the run shares the
-// returned base.  All 64 lanes must call it; lanes with ok == false take part
-// in the vote only.
-__device__ __forceinline__ int run_rank(int cell, bool ok, int lane, int* __restrict__ counts) {
-    const int prev = __shfl_up(cell, 1, 64);
-    const bool head = !ok || lane == 0 || prev != cell;
-    const uint64_t heads = __ballot(head);
-    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1);
-    const uint64_t le = heads & upto;
-    const int leader = 63 - __clzll(static_cast<long long>(le));
-    const uint64_t gt = heads & ~upto;
-    const int next = gt ? __ffsll(static_cast<long long>(gt)) - 1 : 64;
-    int rbase = 0;
-    if (ok && lane == leader) rbase = atomicAdd(counts + cell, next - lane);
-    rbase = __shfl(rbase, leader, 64);
-    return rbase + lane - leader;
-}
-
 // Forward compositing of ray slot `slot` by one wavefront (segs: its 32
 // segment sums in LDS).  With a.target it also forms the photometric
 // gradient dL/dC; every lane returns that gradient in g and log T_end in
@@ -707,13 +686,6 @@ struct BinArgs {
 };
 
 
-__global__ __launch_bounds__(256) void fill_int_kernel(int* __restrict__ p, int64_t n, int v) {
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-        p[i] = v;
-}
-
-
 // Records in binned order when no network backward places them (density
 // only): the head (fractional position, dL/draw) at cell start + rank.
 __global__ __launch_bounds__(256) void bin_place_kernel(BinArgs a) {
@@ -996,87 +968,6 @@ __global__ __launch_bounds__(256) void grid_active_kernel(const float* __restric
         const uint64_t bits = __ballot(nz);
         if (lane == 0) active[v0 >> 5] = static_cast<uint32_t>(bits);
         if (lane == 1 && v0 + 32 < nv) active[(v0 >> 5) + 1] = static_cast<uint32_t>(bits >> 32);
-    }
-}
-
-// Device-wide exclusive scan of int32 counts in three passes.
-__device__ __forceinline__ int block_excl_scan_1024(int v, int* sh, int* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = v;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += y;
-    }
-    if (lane == 63) sh[wave] = incl;
-    __syncthreads();
-    int woff = 0, tot = 0;
-    for (int w = 0; w < 16; ++w) {
-        if (w < wave) woff += sh[w];
-        tot += sh[w];
-    }
-    __syncthreads();
-    *total = tot;
-    return woff + incl - v;
-}
-
-// Eight consecutive counts of one thread (zero past n); 32-byte aligned.
-__device__ __forceinline__ void load8(const int* __restrict__ in, int64_t base, int64_t n, int v[8]) {
-    if (base + 8 <= n) {
-        const int4 a = *reinterpret_cast<const int4*>(in + base);
-        const int4 b = *reinterpret_cast<const int4*>(in + base + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-        for (int u = 0; u < 8; ++u) v[u] = base + u < n ? in[base + u] : 0;
-    }
-}
-
-__global__ __launch_bounds__(1024) void scan_block_sums_kernel(const int* __restrict__ in, int64_t n,
-                                                               long long* __restrict__ bsum) {
-    __shared__ int sh[16];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanPer + threadIdx.x * 8;
-    int v8[8];
-    load8(in, base, n, v8);
-    int v = 0;
-    for (int u = 0; u < 8; ++u) v += v8[u];
-    int tot;
-    block_excl_scan_1024(v, sh, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-// Exclusive scan of the counts: each workgroup adds the totals of all the
-// workgroups before it (read from bsum, summed in the workgroup) to its own
-// in-workgroup scan.
-__global__ __launch_bounds__(1024) void scan_apply_kernel(const int* __restrict__ in, int64_t n,
-                                                          const long long* __restrict__ bsum, int* __restrict__ out) {
-    __shared__ int sh[16];
-    __shared__ long long sp[16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    long long pre = 0;
-    for (int b = threadIdx.x; b < static_cast<int>(blockIdx.x); b += 1024) pre += bsum[b];
-    for (int off = 32; off > 0; off >>= 1) pre += __shfl_xor(pre, off, 64);
-    if (lane == 0) sp[wave] = pre;
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanPer + threadIdx.x * 8;
-    int v[8];
-    load8(in, base, n, v);
-    int loc = 0;
-    for (int u = 0; u < 8; ++u) loc += v[u];
-    int tot;
-    const int ex = block_excl_scan_1024(loc, sh, &tot);   // its barriers also publish sp
-    long long blk = 0;
-    for (int w = 0; w < 16; ++w) blk += sp[w];
-    int run = static_cast<int>(blk) + ex;
-    int o[8];
-    for (int u = 0; u < 8; ++u) {
-        o[u] = run;
-        run += v[u];
-    }
-    if (base + 8 <= n) {
-        *reinterpret_cast<int4*>(out + base) = make_int4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<int4*>(out + base + 4) = make_int4(o[4], o[5], o[6], o[7]);
-    } else {
-        for (int u = 0; u < 8; ++u)
-            if (base + u < n) out[base + u] = o[u];
     }
 }
 
@@ -1475,16 +1366,6 @@ Bins bins_of(const Common& cm, const dvgo_field* field) {
     return b;
 }
 
-// Exclusive scan of the per-cell counts into cell starts.
-int32_t run_cell_scan(const Common& cm, const Bins& b, hipStream_t s) {
-    const int64_t nc1 = b.ncell + 1;
-    const int nb = static_cast<int>((nc1 + kScanPer - 1) / kScanPer);
-    long long* bsum = reinterpret_cast<long long*>(cm.ws + cm.L.scan_tmp);
-    DVGO_LAUNCH(K_CELL_SCAN, scan_block_sums_kernel, dim3(nb), dim3(1024), 0, s, b.cell_count, nc1, bsum);
-    DVGO_LAUNCH(K_CELL_SCAN, scan_apply_kernel, dim3(nb), dim3(1024), 0, s, b.cell_count, nc1, bsum, b.cell_start);
-    return dvgo::launch_status();
-}
-
 // Records placed in binned order (by the network backward, or here when
 // there is none), then one thread per vertex: gradient into the grids, or
 // the grids' fused Adam step.
@@ -1581,7 +1462,7 @@ int32_t render_bwd_impl(const dvgo_field* field, const dvgo_mlp* mlp, const floa
     else
         DVGO_LAUNCH(K_COMPOSE_BWD, compose_bwd_kernel, compose_grid(B), dim3(kComposeThreads), 0, s, ca);
     if (int32_t st = dvgo::launch_status()) return st;
-    if (int32_t st = run_cell_scan(cm, bins, s)) return st;
+    if (int32_t st = run_cell_scan(bins.cell_count, bins.ncell + 1, cm.ws + cm.L.scan_tmp, bins.cell_start, s)) return st;
     int nblk = 0;
     if (mlp) {   // the network adjoint writes each sample's record at its binned position
         ma.cell_rank = bins.cell_rank;

@@ -4,12 +4,13 @@
 // orders of interpolation and activation (Eq. pre_activation,
 // in_activation, post_activation; softplus without shift, alpha(s) =
 // 1 - exp(-s delta)), fitted to a binary target by mean squared error.
-//   pixel kernel   alpha per pixel; for the loss also dL/dalpha = 2(a - T)/N
-//                  and per-workgroup sums of (a - T)^2
-//   vertex kernel  dL/dV per vertex: one wavefront walks the pixels of its
+//   pixel kernel   alpha per pixel; for the loss also the pixel's factor
+//                  dL/dalpha = 2(a - T)/N times its part of the chain to the
+//                  corners, and per-workgroup sums of (a - T)^2
+//   vertex kernel  dL/dV per vertex: a group of lanes walks the pixels of its
 //                  four cells and sums their contributions (no atomics,
-//                  fixed order)
-//   reduce         the loss from the per-workgroup sums, in a fixed order
+//                  fixed order); one more workgroup sums the loss from the
+//                  per-workgroup sums, in a fixed order
 #include "common.hpp"
 
 namespace {
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(kPix) void toy_pixel_kernel(ToyArgs a, const float*
         if (image) image[p] = al;
         if (target) {
             const float r = al - target[p];
-            dalpha[p] = 2.0f * r / static_cast<float>(n);
+            dalpha[p] = 2.0f * r / static_cast<float>(n) * chain;
             r2 = r * r;
         }
     }
@@ -111,54 +112,9 @@ __global__ __launch_bounds__(kPix) void toy_pixel_kernel(ToyArgs a, const float*
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// dL/dV[a][b]: one wavefront per vertex.  The vertex's pixels are those of
-// the rows and columns whose u, v lie within one cell of it (a margin of
-// one pixel on each side; each pixel's own cell decides), dealt to the 64
-// lanes in row-major order; each lane sums its pixels in order and the
-// lanes' sums meet in a fixed butterfly, so the result does not depend on
-// scheduling.
-constexpr int kVertWaves = 4;   // vertices (wavefronts) per workgroup
-
-__global__ __launch_bounds__(64 * kVertWaves) void toy_vertex_kernel(ToyArgs a, const float* __restrict__ dalpha,
-                                                                     float* __restrict__ grad) {
-    const int64_t nv = static_cast<int64_t>(a.gh) * a.gw;
-    const int lane = threadIdx.x & 63;
-    const int64_t vid = static_cast<int64_t>(blockIdx.x) * kVertWaves + (threadIdx.x >> 6);
-    if (vid >= nv) return;
-    const int va = static_cast<int>(vid / a.gw), vb = static_cast<int>(vid % a.gw);
-    const float rows_per = static_cast<float>(a.H) / static_cast<float>(a.gh - 1);
-    const float cols_per = static_cast<float>(a.W) / static_cast<float>(a.gw - 1);
-    const int i_lo = max(0, static_cast<int>(floorf((va - 1) * rows_per)) - 1);
-    const int i_hi = min(a.H - 1, static_cast<int>(ceilf((va + 1) * rows_per)) + 1);
-    const int j_lo = max(0, static_cast<int>(floorf((vb - 1) * cols_per)) - 1);
-    const int j_hi = min(a.W - 1, static_cast<int>(ceilf((vb + 1) * cols_per)) + 1);
-    const int ncol = j_hi - j_lo + 1;
-    const int npix = (i_hi - i_lo + 1) * ncol;
-    const float mine = a.V[vid];
-    // pre and in: the corner's own factor (alpha'(softplus(V)) sigmoid(V),
-    // or sigmoid(V)) is common to every pixel
-    const float own = a.mode == DVGO_TOY_PRE ? a.delta * expf(-softplus_t(mine) * a.delta) * sigmoid_t(mine)
-                      : a.mode == DVGO_TOY_IN ? sigmoid_t(mine) : 1.0f;
-    float g = 0.0f;
-    for (int q = lane; q < npix; q += 64) {
-        const int i = i_lo + q / ncol, j = j_lo + q % ncol;
-        const Bil b = bilinear(a, i, j);
-        const int di = va - b.i0, dj = vb - b.j0;
-        if (di < 0 || di > 1 || dj < 0 || dj > 1) continue;
-        float chain = 1.0f;
-        if (a.mode != DVGO_TOY_PRE) {
-            float c[4];
-            corners(a, b, c);
-            pixel_alpha(a, b, c, &chain);
-        }
-        g += dalpha[static_cast<int64_t>(i) * a.W + j] * chain * b.w[2 * di + dj];
-    }
-    for (int off = 32; off > 0; off >>= 1) g += __shfl_xor(g, off, 64);
-    if (lane == 0) grad[vid] = g * own;
-}
-
-__global__ __launch_bounds__(256) void toy_reduce_kernel(const float* __restrict__ part, int n, float inv_n,
-                                                         float* __restrict__ loss) {
+// The loss from the pixel kernel's sums: thread t adds every 256th in order,
+// then a fixed tree.
+__device__ __forceinline__ void toy_loss(const float* __restrict__ part, int n, float inv_n, float* __restrict__ loss) {
     __shared__ float red[256];
     float s = 0.0f;
     for (int k = threadIdx.x; k < n; k += 256) s += part[k];
@@ -169,6 +125,58 @@ __global__ __launch_bounds__(256) void toy_reduce_kernel(const float* __restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) *loss = red[0] * inv_n;
+}
+
+// dL/dV[a][b] by a group of kSide x kSide lanes.  The vertex's pixels are
+// those whose u, v lie within one cell of it: lane (r, c) of the group takes
+// every kSide-th row and column of that window (widened by the rounding of u
+// and v; each pixel's own cell decides), and the lanes' sums meet in a fixed
+// butterfly, so the result does not depend on scheduling.  Latency-bound: the
+// pixel kernel's factor is read here, where it was evaluated again for every
+// pixel of a window that a whole wavefront walked, 24 -> 4.6 us for a
+// 128 x 128 grid over 256 x 256 pixels (16 pixels a vertex).  The last workgroup
+// takes the loss, which had a launch of its own (4 us).
+template <int kSide>
+__global__ __launch_bounds__(256) void toy_vertex_kernel(ToyArgs a, const float* __restrict__ factor,
+                                                         float* __restrict__ grad, const float* __restrict__ part,
+                                                         int nparts, float inv_n, float* __restrict__ loss) {
+    if (blockIdx.x == gridDim.x - 1) {
+        toy_loss(part, nparts, inv_n, loss);
+        return;
+    }
+    constexpr int kLanes = kSide * kSide;
+    const int64_t nv = static_cast<int64_t>(a.gh) * a.gw;
+    const int l = threadIdx.x % kLanes;
+    const int64_t vid = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / kLanes;
+    if (vid >= nv) return;   // whole groups: 256 is a multiple of kLanes
+    const int va = static_cast<int>(vid / a.gw), vb = static_cast<int>(vid % a.gw);
+    // rows with u = (i + 1/2) su in [va - 1, va + 1), and columns likewise;
+    // u is off by at most 2^-22 of itself, H 2^-22 rows
+    const float rows_per = static_cast<float>(a.H) / static_cast<float>(a.gh - 1);
+    const float cols_per = static_cast<float>(a.W) / static_cast<float>(a.gw - 1);
+    const float mi = 0.51f + 1e-6f * static_cast<float>(a.H), mj = 0.51f + 1e-6f * static_cast<float>(a.W);
+    const int i_lo = max(0, static_cast<int>(floorf((va - 1) * rows_per - mi)));
+    const int i_hi = min(a.H - 1, static_cast<int>(ceilf((va + 1) * rows_per + mi - 1.0f)) - 1);
+    const int j_lo = max(0, static_cast<int>(floorf((vb - 1) * cols_per - mj)));
+    const int j_hi = min(a.W - 1, static_cast<int>(ceilf((vb + 1) * cols_per + mj - 1.0f)) - 1);
+    float g = 0.0f;
+    for (int i = i_lo + l / kSide; i <= i_hi; i += kSide)
+        for (int j = j_lo + l % kSide; j <= j_hi; j += kSide) {
+            const Bil b = bilinear(a, i, j);
+            const int di = va - b.i0, dj = vb - b.j0;
+            const float w = di == 0 ? (dj == 0 ? b.w[0] : b.w[1]) : (dj == 0 ? b.w[2] : b.w[3]);
+            const float f = factor[static_cast<int64_t>(i) * a.W + j];
+            g += di >= 0 && di <= 1 && dj >= 0 && dj <= 1 ? f * w : 0.0f;
+        }
+    #pragma unroll
+    for (int off = kLanes / 2; off > 0; off >>= 1) g += __shfl_xor(g, off, 64);
+    if (l != 0) return;
+    // pre and in: the corner's own factor (alpha'(softplus(V)) sigmoid(V),
+    // or sigmoid(V)) is common to every pixel
+    const float mine = a.V[vid];
+    const float own = a.mode == DVGO_TOY_PRE ? a.delta * expf(-softplus_t(mine) * a.delta) * sigmoid_t(mine)
+                      : a.mode == DVGO_TOY_IN ? sigmoid_t(mine) : 1.0f;
+    grad[vid] = g * own;
 }
 
 int32_t toy_args(const float* V, int32_t gh, int32_t gw, int32_t H, int32_t W, int32_t mode, float delta,
@@ -228,11 +236,18 @@ int32_t dvgo_toy2d_loss_grad(const float* V, int32_t gh, int32_t gw, const float
                 dalpha, part);
     if (int32_t st = dvgo::launch_status()) return st;
     const int64_t nv = static_cast<int64_t>(gh) * gw;
-    DVGO_LAUNCH(K_TOY_VERTEX, toy_vertex_kernel, dim3(static_cast<unsigned>((nv + kVertWaves - 1) / kVertWaves)),
-                dim3(64 * kVertWaves), 0, s, a, dalpha, grad);
-    if (int32_t st = dvgo::launch_status()) return st;
-    DVGO_LAUNCH(K_TOY_REDUCE, toy_reduce_kernel, dim3(1), dim3(256), 0, s, part, nblk,
-                1.0f / static_cast<float>(n), loss);
+    // 4 x 4 lanes a vertex, or 8 x 8 where it has more than 16 pixels (a stride
+    // above 4).  16 and 64 lanes on a 256 x 256 image, launch included: 6.2 and
+    // 9.1 us at stride 2, 6.9 and 6.3 at 4, 7.7 and 6.3 at 6, 12.8 and 10.0 at 16;
+    // on 512 x 512, 10.9 and 21.1 at 2, 7.3 and 10.8 at 4, 15.3 and 9.3 at 16
+    const bool wide = static_cast<int64_t>(H) * W > 16 * nv;
+    const int64_t blocks = (nv * (wide ? 64 : 16) + 255) / 256 + 1;
+    const float inv_n = 1.0f / static_cast<float>(n);
+    const dim3 grid(static_cast<unsigned>(blocks));
+    if (wide)
+        DVGO_LAUNCH(K_TOY_VERTEX, toy_vertex_kernel<8>, grid, dim3(256), 0, s, a, dalpha, grad, part, nblk, inv_n, loss);
+    else
+        DVGO_LAUNCH(K_TOY_VERTEX, toy_vertex_kernel<4>, grid, dim3(256), 0, s, a, dalpha, grad, part, nblk, inv_n, loss);
     return dvgo::launch_status();
 }
 

@@ -347,53 +347,9 @@ __device__ __forceinline__ void sample_inputs(const PosArgs& a, const float* fea
 // bfloat16 matrix cores (v_mfma_f32_32x32x16_bf16): K = 16 per step, 8
 // consecutive K values per lane half; float32 accumulation.
 // ---------------------------------------------------------------------------
-constexpr int kBP = 136;   // LDS pitch (bf16 elements) of a staged feature row
-constexpr int kTP = 128;   // LDS pitch (bf16) of a staged sample row [sample][feature]
-
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-// A staged row is 32 chunks of 8 bytes (4 features); chunk j of sample row r
-// sits at chunk j ^ swz(r).  swz swaps the two low 2-bit fields of the row
-// index, so that both the 16 rows one staging store covers per 16 lanes and
-// the 4 rows x 4 chunks one transpose read covers per 16 lanes land on 16
-// distinct chunk positions modulo 16 (all 32 LDS banks).
-__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
-__device__ __forceinline__ __bf16* chunk_at(__bf16* T, int r, int j) { return T + r * kTP + 4 * (j ^ swz(r)); }
-__device__ __forceinline__ const __bf16* chunk_at(const __bf16* T, int r, int j) {
-    return T + r * kTP + 4 * (j ^ swz(r));
-}
-
-// This lane's packed operand fragment of step st (features phi16(st, 0..7, h),
-// two runs of four) into its sample's row: two 8-byte stores.
-__device__ __forceinline__ void stage_row(__bf16* T, int col_s, int st, int h, const bf16x8& v) {
-    const int j = 8 * (st >> 1) + 4 * (st & 1) + h;   // chunk of features 32(st/2) + 16(st%2) + 4h ..
-    bf16x4 lo, hi;
-    #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        lo[e] = v[e];
-        hi[e] = v[4 + e];
-    }
-    *reinterpret_cast<bf16x4*>(chunk_at(T, col_s, j)) = lo;
-    *reinterpret_cast<bf16x4*>(chunk_at(T, col_s, j + 2)) = hi;
-}
-
-// K-major operand from [sample][feature] rows with two LDS transpose reads:
-// lane (m, h) receives feature col0 + m of samples row0 + 8h .. row0 + 8h + 7.
-// Each read transposes a 16x4 block within a 16-lane group: source lane t of
-// group G addresses sample row0 + 8(G/2) + t/4, features col0 + 16(G%2) + 4(t%4)
-// .. +3, and output lane i of the group receives feature col0 + 16(G%2) + i of
-// those four samples.
-__device__ __forceinline__ bf16x8 tr_operand(const __bf16* T, int row0, int col0, int lane) {
-    const int G = lane >> 4, t = lane & 15;
-    const int r = row0 + 8 * (G >> 1) + (t >> 2), j = (col0 + 16 * (G & 1)) / 4 + (t & 3);
-    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)chunk_at(T, r, j));
-    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)chunk_at(T, r + 4, j));
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x8 ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, ab);
-}
 
 // Round-to-nearest-even bfloat16 pairs of accumulator values, as the packed
 // 32-bit words of an 8-element operand (one v_cvt_pk_bf16_f32 per pair).
@@ -629,490 +585,552 @@ __global__ __launch_bounds__(256, 3) void mlp_fwd_bf16_kernel(MlpArgs a0, PosArg
     }
 }
 
-// NT output tiles of a chained 128-wide layer without the explicit read
-// pipelining (for kernels with two wavefronts per SIMD, where the other
-// wavefront covers the LDS latency).
-template <int NT>
-__device__ __forceinline__ void chain_tiles_plain_bf16(const bf16x8* w, int lane, int mt0, const bf16x8 in[8],
-                                                       f32x16 acc[NT]) {
-    #pragma unroll
-    for (int st = 0; st < 8; ++st)
-        #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = mma_bf16(w[((mt0 + t) * 8 + st) * 64 + lane], in[st], acc[t]);
-}
+constexpr int kSB = 64;   // samples per block
 
-// Inverse of stage_row: this lane's operand fragment of step st read back
-// from its sample's row.
-__device__ __forceinline__ bf16x8 read_row(const __bf16* T, int col_s, int st, int h) {
-    const int j = 8 * (st >> 1) + 4 * (st & 1) + h;
-    const s16x4 lo = *reinterpret_cast<const s16x4*>(chunk_at(T, col_s, j));
-    const s16x4 hi = *reinterpret_cast<const s16x4*>(chunk_at(T, col_s, j + 2));
+// Activation tile of one plane: kSB rows of 16 units of 16 bytes.  Unit
+// 2st + h of a row holds the eight features phi16(st, 0..7, h) that one lane
+// produces and, as the next layer's operand, reads: one 16-byte access each
+// way.  The unit index is permuted by the row, so that eight consecutive rows
+// (one phase of a 16-byte access) and the 4 rows x 2 units of a transpose
+// read's 16 lanes cover all banks.
+__device__ __forceinline__ int unit_swz(int r) { return ((r & 3) << 1) | ((r >> 2) & 1) | (r & 8); }
+
+constexpr int kTile = kSB * kH;             // elements of one plane of an activation tile
+constexpr uint32_t kPlaneB = 2 * kTile;     // its bytes
+constexpr uint32_t kColB = 32 * kH * 2;     // bytes of one column tile's 32 rows
+
+// LDS by byte address, so that one register serves every access that differs
+// by a constant (the instruction's offset field): plane, column tile and K
+// step of an activation tile.
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ uint32_t lds_addr(void* p) { return (uint32_t)(uintptr_t)(lds_char*)p; }
+template <typename T>
+__device__ __forceinline__ T lds_get(uint32_t a) { return *(__attribute__((address_space(3))) const T*)a; }
+template <typename T>
+__device__ __forceinline__ void lds_put(uint32_t a, const T& v) { *(__attribute__((address_space(3))) T*)a = v; }
+
+// K-major operand from two LDS transpose reads (rows r and r + 4 of a lane's
+// samples): see tr_operand for the lanes' roles.
+__device__ __forceinline__ bf16x8 tr_pair(uint32_t a, uint32_t b) {
     typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
+    const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a);
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b);
+    const s16x8 uv = __builtin_shufflevector(u, v, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, uv);
 }
 
-// The per-ray first-layer part of two output tiles mt0, mt0 + 1.
-__device__ __forceinline__ void load_base2(const float* base, int r, int h, int mt0, f32x16 acc[2]) {
-    const float* br = base + static_cast<int64_t>(r) * kH;
+__device__ __forceinline__ float wave_total(float v) {
     #pragma unroll
-    for (int t = 0; t < 2; ++t)
-        #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4*>(br + 32 * (mt0 + t) + 8 * q + 4 * h);
-            acc[t][4 * q + 0] = v.x;
-            acc[t][4 * q + 1] = v.y;
-            acc[t][4 * q + 2] = v.z;
-            acc[t][4 * q + 3] = v.w;
-        }
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
-// bfloat16 network adjoint with eight wavefronts per workgroup (two per
-// SIMD, so that one wavefront's LDS and matrix-core latency hides behind the
-// other's work).  The 128 samples of a block form four groups of 32
-// (g = wave % 4); the two wavefronts of a group split every layer's output
-// features in halves (q = wave / 4: tiles 2q, 2q + 1 of 32), exchanging the
-// other half through the sample-row staging that the weight gradients read
-// anyway.  Weight-gradient accumulators per wavefront: dW2 rows 32g, columns
-// of tiles 2q, 2q + 1; dW1 rows 32g, x' columns of tile q; dW3 (q = 0) or
-// db2 (q = 1) rows 32g.  The two halves of the head's logits and of
-// dL/dfeat are summed through LDS.
+__device__ __forceinline__ f32x16 zero_tile() {
+    f32x16 z;
+    #pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+    return z;
+}
+
+// ---------------------------------------------------------------------------
+// bfloat16 adjoint: weights stationary.  Eight wavefronts per workgroup (two
+// per SIMD) take a block of 128 samples.  Wavefront (w, q) owns the features
+// 32w .. 32w + 31 of every layer for the 64 samples of half q (two column
+// tiles), and of the weight gradients the rows 32w over all 128 samples: of
+// dW2 the columns of tiles 2q and 2q + 1, of dW1 those of tile q.  Its rows of
+// W2, then of W2^T, and its gradients stay in registers; a block's activations
+// pass between the wavefronts as [sample][feature] rows in LDS: the operand of
+// a layer is one 16-byte read per lane and K step for 32 x 32 outputs, that of
+// a weight gradient the same rows through the LDS transpose load.
 //
-// With the encoded position (KX > 0) the first layer takes kS1 K steps, the
-// x' rows hold [f, PE_KX(u), PE(d), 1] (three tiles: the q = 0 wavefronts
-// also accumulate tile 2, whose nine non-zero columns share dX with dW3,
-// moved to columns 29..31), and the next block's inputs are not prefetched
-// (its LDS goes to the wider first-layer operand).
+// Bound by the six phases between barriers, in which the two wavefronts of a
+// SIMD do the same: their 160 matrix instructions per block are 5100 cycles,
+// the vector instructions about 4800 (the head's sigmoid and the packing of
+// rows), a block takes 14,800, of which 4400 are waits at the barriers.
+// Reading the rows of the next K steps while a step's instructions run was
+// worth 3,000 of them, dL/dz1 in rows of its own (one barrier less) 650.
+// The layout before, 32 samples stationary per wavefront pair and the weights
+// read from LDS, took 1.5 times the LDS bytes and eight barriers: 390k samples
+// 93 -> 83 us, 7.1M samples 1610 -> 1383 us, with encoded positions (KX = 5,
+// 203k samples) 80 -> 60 us.
+// ---------------------------------------------------------------------------
 template <int KX>
 __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArgs pa) {
     using L = NetLayout<KX>;
     constexpr int kS1 = L::kS1;
-    constexpr bool kPre = KX == 0;   // the next block's layer-1 inputs prefetched into LDS
-    // dX columns of dW3 (q = 0): 0..2, or 29..31 when x' tile 2 takes
-    // columns 0..8 (x' columns 64..72; its columns 73..95 are zero)
-    constexpr int kW3Col = KX > 0 ? 29 : 0;
-    static_assert(KX == 0 || NetLayout<KX>::kIn + 1 - 64 <= kW3Col, "x' tile 2 and dW3 share dX");
-    __shared__ bf16x8 sW2[kW2PackBF16 / 8];
-    __shared__ bf16x8 sW2T[kW2PackBF16 / 8];
-    __shared__ bf16x8 sW1[4 * kS1 * 64];
-    __shared__ __attribute__((aligned(16))) __bf16 tA[128 * kTP];   // h1 then dL/dz1, [sample][feature]
-    __shared__ __attribute__((aligned(16))) __bf16 tB[128 * kTP];   // h2, then dL/dz2, then x'
-    // dL/dz3 [channel][sample]: rows 0..2, row 3 zero (the B operand rows of
-    // lanes m >= 3)
-    __shared__ __attribute__((aligned(16))) __bf16 sC[4 * kBP];
+    constexpr int kXP = KX > 0 ? 112 : 80;          // pitch of an x' row: 4 rows of a transpose read on distinct banks
+    constexpr int kGroups = (L::kIn + 1 + 7) / 8;   // 8-column groups of x' = [inputs, PE(d), 1]
+    constexpr int kXF = 8 * kGroups + 4;            // pitch of the float32 x' rows (KX > 0)
+    constexpr int kCP = 72;                         // pitch of a dz3 row (samples)
+    constexpr int kS = 128;                         // samples per block
+    constexpr int kZB = kS * kH * 2, kDB = 4 * kS * kC * 4;
+    __shared__ __attribute__((aligned(256))) __bf16 sH[kS * kH];    // h1
+    __shared__ __attribute__((aligned(256))) __bf16 sG[kS * kH];    // dL/dz1
+    // h2 (own rows and columns), then dL/dz2; the wavefronts' logits, then
+    // their dL/dfeat; between two blocks the float32 x' rows share both
+    __shared__ __attribute__((aligned(256))) char sU[kZB + kDB];
+    __shared__ __attribute__((aligned(256))) __bf16 sX[kS * kXP];   // x'
+    __shared__ __attribute__((aligned(16))) __bf16 sCs[8][4 * kCP]; // dL/dz3 [channel][sample], row 3 zero
     __shared__ __attribute__((aligned(16))) float sB2[kH];
-    __shared__ float sB3[4];
-    // The halves' logit partials (until B3) and the second half's dL/dfeat
-    // partial (B6 .. B7) share one buffer.
-    __shared__ __attribute__((aligned(16))) float sX[128 * kC];
-    float4 (*sZ)[128] = reinterpret_cast<float4 (*)[128]>(sX);
-    float (*sD)[kC] = reinterpret_cast<float (*)[kC]>(sX);
-    // Packed operands of the head (W3, W3^T) and of dL/dfeat (W1[:, :12]^T),
-    // only the lanes whose fragments are not zero: W3 rows 0..2 and W1^T
-    // rows 0..11 (both lane halves), W3^T's lane half 0 (its K is the three
-    // colour channels).  Other lanes use a zero fragment.
-    __shared__ bf16x8 sW3c[8 * 2 * 3];
-    __shared__ bf16x8 sW3Tc[4 * 32];
-    __shared__ bf16x8 sW1Tc[8 * 2 * kC];
-    // The next block's layer-1 inputs, copied straight from global memory to
-    // LDS during the current block (no registers): the first-layer rows of
-    // the rays r0 .. r0 + kPreRays - 1 (r0: the ray of the block's first
-    // sample) and the features of the block's 128 samples.
-    constexpr int kPreRays = 8;
-    __shared__ __attribute__((aligned(16))) float sPB[kPre ? kPreRays * kH : 4];
-    __shared__ __attribute__((aligned(16))) float sPF[kPre ? 128 * kC : 4];
-    __shared__ float sRed[4 * 4];
-    {   // every operand this kernel keeps in LDS: all loads first, then the stores
-        Frags<512, kW2PackBF16 / 8> f2, f2t;
-        Frags<512, 4 * kS1 * 64> f1;
-        f2.load(reinterpret_cast<const bf16x8*>(a0.w2pb));
-        f2t.load(reinterpret_cast<const bf16x8*>(a0.w2tpb));
-        f1.load(reinterpret_cast<const bf16x8*>(a0.w1pb));
-        // the compact operands, at most one fragment per thread each;
-        // fragment (st, lane) of a packed operand is at st * 64 + lane
-        const int ti = static_cast<int>(threadIdx.x);
-        const bf16x8* g3 = reinterpret_cast<const bf16x8*>(a0.w3pb);
-        const bf16x8* g3t = reinterpret_cast<const bf16x8*>(a0.w3tpb);
-        const bf16x8* g1t = reinterpret_cast<const bf16x8*>(a0.w1tpb);
-        bf16x8 c3, c3t, c1t;
-        if (ti < 8 * 2 * 3) c3 = g3[(ti / 6) * 64 + 32 * ((ti / 3) & 1) + ti % 3];
-        if (ti < 4 * 32) c3t = g3t[(ti / 32) * 64 + ti % 32];
-        if (ti < 8 * 2 * kC) c1t = g1t[(ti / (2 * kC)) * 64 + 32 * ((ti / kC) & 1) + ti % kC];
-        const float b2 = threadIdx.x < kH ? a0.b2[threadIdx.x] : 0.0f;
-        const float b3 = threadIdx.x < 3 ? a0.b3[threadIdx.x] : 0.0f;
-        f2.store(sW2);
-        f2t.store(sW2T);
-        f1.store(sW1);
-        if (ti < 8 * 2 * 3) sW3c[ti] = c3;
-        if (ti < 4 * 32) sW3Tc[ti] = c3t;
-        if (ti < 8 * 2 * kC) sW1Tc[ti] = c1t;
-        if (threadIdx.x < kH) sB2[threadIdx.x] = b2;
-        if (threadIdx.x < 3) sB3[threadIdx.x] = b3;
-    }
-    for (int i = threadIdx.x; i < 4 * kBP; i += blockDim.x) sC[i] = static_cast<__bf16>(0.0f);
-    __syncthreads();
+    __shared__ float sRed[4];
+    static_assert(kS * kXF * 4 <= kZB + kDB, "the float32 x' rows share sU");
+    __bf16* sZ = reinterpret_cast<__bf16*>(sU);
+    float (*sL)[kS][4] = reinterpret_cast<float (*)[kS][4]>(sU + kZB);
+    float (*sD)[kS][kC] = reinterpret_cast<float (*)[kS][kC]>(sU + kZB);
+    float* sXF = reinterpret_cast<float*>(sU);
     const int64_t n = *a0.n_kept < a0.cap ? *a0.n_kept : a0.cap;
-    // The wavefront index in a scalar register: the role branches below are
-    // then scalar branches.  Under a vector-masked branch a matrix
-    // instruction still updates its accumulator in a wavefront whose mask is
-    // empty.
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = wave & 3, q = wave >> 2;
+    // The wavefront index in a scalar register: role branches are scalar
+    // branches then.  Under a vector-masked branch a matrix instruction still
+    // updates its accumulator in a wavefront whose mask is empty.
+    const int t = static_cast<int>(threadIdx.x);
+    const int lane = t & 63, wave8 = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int q = wave8 >> 2, wave = wave8 & 3;
     const int m = lane & 31, h = lane >> 5;
-    const int col_s = g * 32 + m;     // this lane's sample column in the staged block
-    f32x16 dW2[2], dW1, dX;           // dX: dW3 and (KX > 0) x' tile 2 (q = 0), or db2 (q = 1)
-    #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-        dW2[0][rr] = 0.0f;
-        dW2[1][rr] = 0.0f;
-        dW1[rr] = 0.0f;
-        dX[rr] = 0.0f;
-    }
-    float db3[3] = {0, 0, 0};
-    bf16x8 ones, zero8;
+    __bf16* sC = sCs[wave8];
+    // dW2, dW1: as above; over the half's own samples: dX (dW3 in columns
+    // 0..2, db2 in column 3) and (KX > 0) dW1's third tile
+    f32x16 dW2[2] = {zero_tile(), zero_tile()}, dW1 = zero_tile(), dW1c = zero_tile(), dX = zero_tile();
+    float db3[3] = {0.0f, 0.0f, 0.0f};
+    bf16x8 one3, zero8;   // a ones column 3
     #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        ones[e] = static_cast<__bf16>(m == 0 ? 1.0f : 0.0f);
+        one3[e] = static_cast<__bf16>(m == 3 ? 1.0f : 0.0f);
         zero8[e] = static_cast<__bf16>(0.0f);
     }
-    // Block b's layer-1 inputs into sPB / sPF, by every wavefront: waves
-    // 0..3 copy a 1 KB piece of sPB each (two 512-byte rows; rows past the
-    // last ray read the last), waves 4..7 and 0..1 the six 1 KB pieces of
-    // sPF (addresses past the capacity read the last feature quad).  The
-    // copies land asynchronously; a wait on all memory operations precedes
-    // the barrier before their use.
-    typedef __attribute__((address_space(3))) void lds_void;
-    auto prefetch = [&](const MlpArgs& a, int64_t b, int r0) {
-        if constexpr (!kPre) return;
-        if (wave < 4) {
-            const int row = 2 * wave + (lane >> 5);
-            const int rr = r0 + row < a.nrays ? r0 + row : a.nrays - 1;
-            __builtin_amdgcn_global_load_lds(a.base + static_cast<int64_t>(rr) * kH + 4 * (lane & 31),
-                                             (lds_void*)(sPB + 256 * wave), 16, 0, 0);
-        }
-        if (wave >= 4 || wave < 2) {
-            const int piece = wave >= 4 ? wave - 4 : wave + 4;
-            const int64_t fmax = a.cap * kC - 4;
-            int64_t fo = b * 128 * kC + 256 * piece + 4 * lane;
-            fo = fo < fmax ? fo : fmax;
-            __builtin_amdgcn_global_load_lds(a.feat + fo, (lds_void*)(sPF + 256 * piece), 16, 0, 0);
+    // the wavefront's rows of W2 (layer 2) or W2^T (its adjoint): one register
+    // set, refilled from the L2 (both, and the smaller operands, did not fit:
+    // 103 registers spilled)
+    bf16x8 wf[8];
+    auto load_w = [&](const uint16_t* w, int st) {
+        wf[st] = (reinterpret_cast<const bf16x8*>(w) + wave * 512 + st * 64)[lane];
+    };
+    for (int i = t; i < kS * kXP / 8; i += 512) reinterpret_cast<bf16x8*>(sX)[i] = zero8;   // columns past the last group
+    for (int i = lane; i < kCP; i += 64) sC[3 * kCP + i] = static_cast<__bf16>(0.0f);
+    if (threadIdx.x < kH) sB2[threadIdx.x] = a0.b2[threadIdx.x];
+    const float b3[3] = {a0.b3[0], a0.b3[1], a0.b3[2]};
+    __syncthreads();
+    const int xrow = t >> 2, xq = t & 3;   // the x' row and first column group this thread stages
+    // A block's samples by a scalar base and a 32-bit lane offset (the last
+    // block's missing samples read its last one).
+    const int nblocks = static_cast<int>((n + kS - 1) / kS);
+    auto last_of = [&](int blk) {
+        const int64_t left = n - static_cast<int64_t>(blk) * kS;
+        return static_cast<int>(left < kS ? left : kS) - 1;
+    };
+    const int col0 = 64 * q + m;   // this lane's first column's sample (the second is 32 on)
+    // the rays of the next block's samples (this lane's two columns, and this
+    // thread's x' row), loaded a block ahead
+    int r_n[2], xr_n;
+    auto load_rays = [&](const MlpArgs& a, int blk) {
+        const int* sr = a.sample_ray + static_cast<int64_t>(blk) * kS;
+        const int last = last_of(blk);
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) r_n[c] = sr[min(32 * c + col0, last)];
+        xr_n = sr[min(xrow, last)];
+    };
+    // this thread's x' columns (KX == 0), loaded while the block before ends
+    float4 xin[4];
+    auto load_x = [&](const MlpArgs& a, int blk) {
+        if constexpr (KX == 0) {
+            // groups: f[0..7] | f[8..11], PE[0..3] | PE[4..11] | PE[12..19] | PE[20..26], 1
+            const float* f = a.feat + static_cast<int64_t>(blk) * (kS * kC) + min(xrow, last_of(blk)) * kC;
+            const float* pe = a.pe + static_cast<int64_t>(xr_n) * 32;
+            xin[0] = *reinterpret_cast<const float4*>(xq < 2 ? f + 8 * xq : pe + 8 * xq - 12);
+            xin[1] = *reinterpret_cast<const float4*>(xq < 1 ? f + 4 : pe + 8 * xq - 8);
+            xin[2] = *reinterpret_cast<const float4*>(pe + 20);
+            xin[3] = *reinterpret_cast<const float4*>(pe + 24);
         }
     };
-    int r_next = 0, r0 = 0;   // r0: the ray of the current block's first sample (scalar)
-    if (static_cast<int64_t>(blockIdx.x) * 128 < n) {
-        const int64_t s0 = static_cast<int64_t>(blockIdx.x) * 128 + col_s;
-        r_next = a0.sample_ray[s0 < n ? s0 : n - 1];
-        r0 = __builtin_amdgcn_readfirstlane(a0.sample_ray[static_cast<int64_t>(blockIdx.x) * 128]);
-        prefetch(a0, blockIdx.x, r0);
+    if (static_cast<int>(blockIdx.x) < nblocks) {
+        load_rays(a0, blockIdx.x);
+        load_x(a0, blockIdx.x);
+        #pragma unroll
+        for (int st = 0; st < 8; ++st) load_w(a0.w2pb, st);
     }
-    __builtin_amdgcn_s_waitcnt(0);   // the first block's copies (and r_next)
-    __syncthreads();
-    for (int64_t blk = blockIdx.x; blk * 128 < n; blk += gridDim.x) {
+    // acc += wf * (rows of an activation tile); the rows of the next kAhead K
+    // steps are on their way from LDS while a step's instructions run
+    auto chain = [&](uint32_t row, f32x16 acc[2]) {
+        constexpr int kAhead = 3;
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 B[kAhead + 1][2];
+        auto rd = [&](int st) {
+            #pragma unroll
+            for (int c = 0; c < 2; ++c) B[st % (kAhead + 1)][c] = lds_get<bf16x8>((row ^ (32u * st)) + c * kColB);
+        };
+        #pragma unroll
+        for (int st = 0; st < kAhead; ++st) rd(st);
+        #pragma unroll
+        for (int st = 0; st < 8; ++st) {
+            if (st + kAhead < 8) rd(st + kAhead);
+            #pragma unroll
+            for (int c = 0; c < 2; ++c) acc[c] = mma_bf16(wf[st], B[st % (kAhead + 1)][c], acc[c]);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAhead, 0);
+        #pragma unroll
+        for (int st = 0; st < 8; ++st) {
+            if (st + kAhead < 8) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // operand of a feature tile over samples 16st .. 16st + 15
+    auto tr_unit = [&](uint32_t at, int st) {
+        const uint32_t off = st * (16 * kH * 2);
+        return tr_pair(at + off, (at ^ 16u) + 4 * kH * 2 + off);
+    };
+    for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         const MlpArgs a = refresh(a0);
-        const int64_t s = blk * 128 + col_s;
-        const bool ok = s < n;
-        const int64_t sc = ok ? s : n - 1;
-        const int r = r_next;
-        const bool more = (blk + gridDim.x) * 128 < n;
-        int r0_next = r0;
-        if (more) {
-            const int64_t s1 = (blk + gridDim.x) * 128 + col_s;
-            r_next = a.sample_ray[s1 < n ? s1 : n - 1];
-            r0_next = a.sample_ray[(blk + gridDim.x) * 128];
-        }
-        // per-sample inputs of the head and of the record, issued here so
-        // that their latency hides behind layers 1 and 2.  Every lane loads
-        // (at a clamped, valid index): a load under a lane-dependent branch
-        // is waited on inside that branch.
-        const float4 dc = reinterpret_cast<const float4*>(a.col)[sc];
-        const int2 cr = a.cell_rank[sc];
-        const float4 rh = a.rec_head[sc];
-        // ---- layer 1, this half's two tiles, staged as h1 rows
-        {
-            // features and the ray's first-layer row from the copies in LDS
-            // (a ray outside the copied rows reads global memory); a sample
-            // past the end takes zero inputs, its copy may be stale.  With
-            // the encoded position: features and row from global memory, the
-            // encoding evaluated here.
-            float xs[L::kS];
-            f32x16 h1[2];
-            if constexpr (kPre) {
-                load_feat(sPF, col_s, xs);
-                const unsigned d = static_cast<unsigned>(r - r0);
-                if (d < static_cast<unsigned>(kPreRays)) load_base2(sPB, static_cast<int>(d), h, 2 * q, h1);
-                else load_base2(a.base, r, h, 2 * q, h1);
-            } else {
-                sample_inputs<KX>(pa, a.feat, sc, r, xs);
-                load_base2(a.base, r, h, 2 * q, h1);
-            }
+        // the next block of this workgroup, or (the last time) this one again
+        const int next = blk + static_cast<int>(gridDim.x) < nblocks ? blk + static_cast<int>(gridDim.x) : blk;
+        const int64_t s0 = static_cast<int64_t>(blk) * kS;
+        const int last = last_of(blk);
+        const int xi = min(xrow, last);   // this thread's x' and record sample
+        // this lane's LDS addresses (hidden from the optimiser, which would
+        // otherwise keep every sum of them in a register of its own):
+        // its sample's row, unit h; the unit it stages; the first of its two
+        // transpose reads of feature tile nt (the second is 4 rows on, where
+        // the unit permutation differs in its lowest bit)
+        const int tG = lane >> 4, tt = lane & 15, trow = 8 * (tG >> 1) + (tt >> 2);
+        const uint32_t tsub = trow * 256 + 8 * ((tt & 3) >> 1), tu = 2 * (tG & 1) + (tt & 1);
+        uint32_t rowH = lds_addr(sH) + col0 * 256 + 16 * (h ^ unit_swz(m));
+        uint32_t rowZ = lds_addr(sZ) + col0 * 256 + 16 * (h ^ unit_swz(m));
+        uint32_t putH = rowH ^ (64u * wave), putZ = rowZ ^ (64u * wave);
+        uint32_t putG = lds_addr(sG) + (putH - lds_addr(sH));
+        uint32_t trH = lds_addr(sH) + tsub + 16 * (tu ^ unit_swz(trow));
+        uint32_t trZ = (lds_addr(sZ) + tsub + 16 * (tu ^ unit_swz(trow))) ^ (64u * wave);
+        uint32_t trG = (lds_addr(sG) + tsub + 16 * (tu ^ unit_swz(trow))) ^ (64u * wave);
+        uint32_t colX = lds_addr(sX) + (col0 * kXP + 8 * h) * 2;
+        uint32_t trX = lds_addr(sX) + (trow * kXP + 16 * (tG & 1) + 4 * (tt & 3)) * 2;
+        uint32_t putX = lds_addr(sX) + xrow * kXP * 2;
+        asm volatile("" : "+v"(rowH), "+v"(rowZ), "+v"(putH), "+v"(putZ), "+v"(putG), "+v"(trH), "+v"(trZ), "+v"(trG),
+                     "+v"(colX), "+v"(trX), "+v"(putX));
+        // this block's loads, in the order of their use: the wavefront's rows
+        // of the first layer's per-ray part, W1, inputs of the head and the
+        // records
+        float4 base4[2][4];
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float4* br = reinterpret_cast<const float4*>(a.base + static_cast<int64_t>(r_n[c]) * kH) + 8 * wave + h;
             #pragma unroll
-            for (int st = 0; st < kS1; ++st) {
-                const bf16x8 fb = ok ? layer1_operand<KX>(xs, st, h) : zero8;
-                #pragma unroll
-                for (int t = 0; t < 2; ++t) h1[t] = mma_bf16(sW1[((2 * q + t) * kS1 + st) * 64 + lane], fb, h1[t]);
-            }
-            #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                #pragma unroll
-                for (int gg = 0; gg < 2; ++gg) stage_row(tA, col_s, 4 * q + 2 * t + gg, h, relu_pack8(h1[t], gg));
+            for (int q = 0; q < 4; ++q) base4[c][q] = br[2 * q];
         }
-        __syncthreads();   // B1: h1 rows complete; sPB, sPF read
-        // ---- layer 2 and the head on this half
+        bf16x8 w1f[kS1];
+        #pragma unroll
+        for (int st = 0; st < kS1; ++st)
+            w1f[st] = (reinterpret_cast<const bf16x8*>(a.w1pb) + (wave * kS1 + st) * 64)[lane];
+        const int xr = xr_n;
+        // ---- x' rows
+        auto put_x = [&](int col, const float4& u, const float4& v) {
+            const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+            bf16x8 b;
+            #pragma unroll
+            for (int e = 0; e < 8; ++e) b[e] = static_cast<__bf16>(x[e]);
+            lds_put(putX + 2 * col, b);
+        };
+        if constexpr (KX == 0) {
+            put_x(8 * xq, xin[0], xin[1]);
+            if (xq == 0) put_x(32, xin[2], xin[3]);
+        } else {
+            // the four threads of a row evaluate the encoded position (thread
+            // q frequency q, thread 3 also frequency 4) and copy the rest
+            float* row = sXF + xrow * kXF;
+            float x[3], u[3], o[3], d[3];
+            #pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                o[i] = pa.rays_o[3 * xr + i];
+                d[i] = pa.rays_d[3 * xr + i];
+            }
+            const float tk = dvgo_dev::recipe_tk(pa.t_near[xr], pa.jitter ? pa.jitter[xr] : 0.0f,
+                                                 (pa.sample_k + s0)[xi], pa.step);
+            dvgo_dev::recipe_x(o, d, tk, x);
+            #pragma unroll
+            for (int i = 0; i < 3; ++i) u[i] = (x[i] - pa.pe_c[i]) * pa.pe_ih[i];
+            const float* f = a.feat + s0 * kC + xi * kC;
+            const float* pe = a.pe + static_cast<int64_t>(xr) * 32;
+            // features by threads 0..2, the view encoding (32 values) by all
+            if (xq < 3) *reinterpret_cast<float4*>(row + 4 * xq) = *reinterpret_cast<const float4*>(f + 4 * xq);
+            const float4 e0 = *reinterpret_cast<const float4*>(pe + 8 * xq);
+            const float4 e1 = *reinterpret_cast<const float4*>(pe + 8 * xq + 4);
+            const float ev[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
+            #pragma unroll
+            for (int e = 0; e < 8; ++e) row[L::kS + 8 * xq + e] = ev[e];
+            if (xq == 0) {
+                #pragma unroll
+                for (int i = 0; i < 3; ++i) row[kC + i] = u[i];
+            }
+            for (int j = xq; j < KX; j += xq == 3 ? 1 : KX) {
+                #pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    float sv, cv;
+                    dvgo_dev::pe_sincos(u[i] * static_cast<float>(1 << j), &sv, &cv);
+                    row[kC + 3 + 6 * j + i] = sv;
+                    row[kC + 6 + 6 * j + i] = cv;
+                }
+            }
+            // the four threads of a row are lanes of one wavefront: its LDS
+            // accesses are in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int g = xq; g < kGroups; g += 4)
+                put_x(8 * g, *reinterpret_cast<const float4*>(row + 8 * g),
+                      *reinterpret_cast<const float4*>(row + 8 * g + 4));
+        }
+        f32x16 h1[2];
+        #pragma unroll
+        for (int c = 0; c < 2; ++c)
+            #pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                h1[c][4 * q] = base4[c][q].x;
+                h1[c][4 * q + 1] = base4[c][q].y;
+                h1[c][4 * q + 2] = base4[c][q].z;
+                h1[c][4 * q + 3] = base4[c][q].w;
+            }
+        __syncthreads();   // x' rows complete
+        // ---- layer 1 (columns past the per-sample inputs meet zero weights)
+        #pragma unroll
+        for (int st = 0; st < kS1; ++st)
+            #pragma unroll
+            for (int c = 0; c < 2; ++c)
+                h1[c] = mma_bf16(w1f[st], lds_get<bf16x8>(colX + (32 * c * kXP + 16 * st) * 2), h1[c]);
+        #pragma unroll
+        for (int c = 0; c < 2; ++c)
+            #pragma unroll
+            for (int g = 0; g < 2; ++g) lds_put((g ? putH ^ 32u : putH) + c * kColB, relu_pack8(h1[c], g));
+        // inputs of the later phases, and the next block's rays
+        load_rays(a, next);
+        bf16x8 w3[2];
+        #pragma unroll
+        for (int g = 0; g < 2; ++g) w3[g] = (reinterpret_cast<const bf16x8*>(a.w3pb) + (2 * wave + g) * 64)[lane];
+        const bf16x8 w3t = (reinterpret_cast<const bf16x8*>(a.w3tpb) + wave * 64)[lane];
+        float4 dc[2];
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) dc[c] = (reinterpret_cast<const float4*>(a.col) + s0)[min(32 * c + col0, last)];
+        const int2 cr = (a.cell_rank + s0)[xi];
         f32x16 z2[2];
         #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int q = 0; q < 4; ++q) {
+            const float4 b = *reinterpret_cast<const float4*>(sB2 + 32 * wave + 8 * q + 4 * h);
             #pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const float4 b = *reinterpret_cast<const float4*>(sB2 + 32 * (2 * q + t) + 8 * qq + 4 * h);
-                z2[t][4 * qq] = b.x;
-                z2[t][4 * qq + 1] = b.y;
-                z2[t][4 * qq + 2] = b.z;
-                z2[t][4 * qq + 3] = b.w;
+            for (int c = 0; c < 2; ++c) {
+                z2[c][4 * q] = b.x;
+                z2[c][4 * q + 1] = b.y;
+                z2[c][4 * q + 2] = b.z;
+                z2[c][4 * q + 3] = b.w;
             }
-        {
-            bf16x8 hb[8];
-            #pragma unroll
-            for (int st = 0; st < 8; ++st) hb[st] = read_row(tA, col_s, st, h);
-            chain_tiles_plain_bf16<2>(sW2, lane, 2 * q, hb, z2);
         }
-        bf16x8 h2h[4];   // bf16(relu(z2)) of this half, steps 4q .. 4q + 3
-        f32x16 z3;
+        __syncthreads();   // h1 rows complete
+        // ---- layer 2, the wavefront's share of the logits, h2 into its own columns of sZ
+        chain(rowH, z2);
         #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) z3[rr] = (q == 0 && h == 0 && rr < 3) ? sB3[rr < 3 ? rr : 0] : 0.0f;
+        for (int st = 0; st < 8; ++st) load_w(a.w2tpb, st);
+        bf16x8 w1t[2];   // for dL/dfeat
+        #pragma unroll
+        for (int g = 0; g < 2; ++g) w1t[g] = (reinterpret_cast<const bf16x8*>(a.w1tpb) + (2 * wave + g) * 64)[lane];
+        bf16x8 h2[2][2];
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            f32x16 z3 = zero_tile();
+            #pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                h2[c][g] = relu_pack8(z2[c], g);
+                lds_put((g ? putZ ^ 32u : putZ) + c * kColB, h2[c][g]);
+                z3 = mma_bf16(w3[g], h2[c][g], z3);
+            }
+            if (h == 0) *reinterpret_cast<float4*>(sL[wave][32 * c + col0]) = make_float4(z3[0], z3[1], z3[2], 0.0f);
+        }
+        const int slot = a.cell_start[cr.x];
+        const float4 rh = (a.rec_head + s0)[xi];
+        __syncthreads();   // logits complete
+        // ---- dz3 (lane half 0), dW3 over the block's samples, dz2 = (W3^T bf16(dz3)) * relu'(z2)
+        // (lane half h takes the sample of column tile h; the operand of both
+        // tiles is in lane half 0)
+        bf16x8 dzb[2] = {zero8, zero8}, h2t[4];
+        #pragma unroll
+        for (int st = 0; st < 4; ++st) h2t[st] = tr_unit(trZ + q * (4 * 16 * kH * 2), st);   // the half's own samples
         {
+            float z[3] = {b3[0], b3[1], b3[2]};
             #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                #pragma unroll
-                for (int gg = 0; gg < 2; ++gg) {
-                    const int st = 4 * q + 2 * t + gg;
-                    h2h[2 * t + gg] = relu_pack8(z2[t], gg);
-                    stage_row(tB, col_s, st, h, h2h[2 * t + gg]);
-                    z3 = mma_bf16(m < 3 ? sW3c[(st * 2 + h) * 3 + (m < 3 ? m : 0)] : zero8, h2h[2 * t + gg], z3);
-                }
-        }
-        if (h == 0) sZ[q][col_s] = make_float4(z3[0], z3[1], z3[2], 0.0f);
-        __syncthreads();   // B2: h2 rows and both logit halves complete
-        // The next block's copies, issued after layers 1 and 2 (the wait on
-        // its first ray, loaded with this block's first loads, then costs
-        // little) and before this block's record-slot load (which that wait
-        // would otherwise include).
-        if (more) prefetch(a, blk + gridDim.x, __builtin_amdgcn_readfirstlane(r0_next));
-        const int slot0 = a.cell_start[cr.x];   // every lane, as above
-        float dz3[3] = {0, 0, 0};
-        if (h == 0) {
-            const float4 z0 = sZ[0][col_s], z1 = sZ[1][col_s];
-            const float zz[3] = {z0.x + z1.x, z0.y + z1.y, z0.z + z1.z};
-            if (ok) {
-                const float dcc[3] = {dc.x, dc.y, dc.z};
-                #pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const float cv = 1.0f / (1.0f + expf(-zz[t]));
-                    dz3[t] = dcc[t] * cv * (1.0f - cv);
-                }
+            for (int w = 0; w < 4; ++w) {
+                const float4 v = *reinterpret_cast<const float4*>(sL[w][32 * h + col0]);
+                z[0] += v.x;
+                z[1] += v.y;
+                z[2] += v.z;
             }
-            if (q == 0) {
-                #pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    sC[t * kBP + col_s] = static_cast<__bf16>(dz3[t]);
-                    db3[t] += dz3[t];
-                }
+            const float g[3] = {h ? dc[1].x : dc[0].x, h ? dc[1].y : dc[0].y, h ? dc[1].z : dc[0].z};
+            const float on = 32 * h + col0 <= last ? 1.0f : 0.0f;
+            #pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float cv = 1.0f / (1.0f + expf(-z[ch]));
+                const float dz3 = on > 0.0f ? g[ch] * cv * (1.0f - cv) : 0.0f;
+                db3[ch] += dz3;
+                const __bf16 b = static_cast<__bf16>(dz3);
+                sC[ch * kCP + 32 * h + m] = b;
+                const uint32_t own = __builtin_bit_cast(uint16_t, b), other = __shfl_xor(own, 32, 64);
+                dzb[0][ch] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(h ? 0u : own));
+                dzb[1][ch] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(h ? 0u : other));
             }
         }
-        // dz2 of this half = (W3^T bf16(dz3)) * relu'(z2)
-        bf16x8 zh[4];
+        #pragma unroll
+        for (int st = 0; st < 4; ++st)
+            dX = mma_bf16(h2t[st], *reinterpret_cast<const bf16x8*>(sC + (m < 3 ? m : 3) * kCP + 16 * st + 8 * h),
+                          dX);
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            f32x16 dh = zero_tile();
+            dh = mma_bf16(w3t, dzb[c], dh);
+            #pragma unroll
+            for (int g = 0; g < 2; ++g)
+                lds_put((g ? putZ ^ 32u : putZ) + c * kColB, relu_grad_pack8(dh, g, h2[c][g]));
+        }
+        load_x(a, next);
+        __syncthreads();   // dz2 rows complete
+        // ---- dh1 = W2^T dz2, dz1 = dh1 * relu'(h1), this wavefront's share of dL/dfeat = W1[:, :12]^T dz1
+        f32x16 dh1[2] = {zero_tile(), zero_tile()};
+        chain(rowZ, dh1);
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            f32x16 df = zero_tile();
+            #pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const bf16x8 d1 = relu_grad_pack8(dh1[c], g, lds_get<bf16x8>((g ? putH ^ 32u : putH) + c * kColB));
+                lds_put((g ? putG ^ 32u : putG) + c * kColB, d1);
+                df = mma_bf16(w1t[g], d1, df);
+            }
+            // rows 0..11 of the tile: registers 0..3 are channels 4h .. 4h + 3,
+            // registers 4..7 (half 0) channels 8..11
+            *reinterpret_cast<float4*>(&sD[wave][32 * c + col0][4 * h]) = make_float4(df[0], df[1], df[2], df[3]);
+            if (h == 0) *reinterpret_cast<float4*>(&sD[wave][32 * c + col0][8]) = make_float4(df[4], df[5], df[6], df[7]);
+        }
+        // ---- dW2 rows 32w, tiles 2q and 2q + 1 over the block's samples, db2
+        // (through the ones column) over the half's own
         {
-            bf16x8 dzb;
-            #pragma unroll
-            for (int e = 0; e < 8; ++e) dzb[e] = static_cast<__bf16>(e < 3 ? dz3[e < 3 ? e : 0] : 0.0f);
-            #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                f32x16 dh;
+            constexpr int kAhead = 2;
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t trB[2] = {trH ^ (128u * q), trH ^ (128u * q + 64u)};
+            bf16x8 A[kAhead + 1], B[kAhead + 1][2];
+            auto rd = [&](int st) {
+                A[st % (kAhead + 1)] = tr_unit(trZ, st);
                 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) dh[rr] = 0.0f;
-                dh = mma_bf16(h == 0 ? sW3Tc[(2 * q + t) * 32 + m] : zero8, dzb, dh);
-                #pragma unroll
-                for (int gg = 0; gg < 2; ++gg) zh[2 * t + gg] = relu_grad_pack8(dh, gg, h2h[2 * t + gg]);
-            }
-        }
-        __syncthreads();   // B3: dz3 rows complete
-        if (q == 0) {      // dW3^T rows 32g over the 128 staged samples
+                for (int c = 0; c < 2; ++c) B[st % (kAhead + 1)][c] = tr_unit(trB[c], st);
+            };
+            #pragma unroll
+            for (int st = 0; st < kAhead; ++st) rd(st);
             #pragma unroll
             for (int st = 0; st < 8; ++st) {
-                const bf16x8 av = tr_operand(tB, 16 * st, 32 * g, lane);
-                const int cm = m - kW3Col;   // dz3 channel of this lane's column (row 3 of sC is zero)
-                const bf16x8 bv = *reinterpret_cast<const bf16x8*>(sC + (cm >= 0 && cm < 3 ? cm : 3) * kBP + 16 * st + 8 * h);
-                dX = mma_bf16(av, bv, dX);
+                if (st + kAhead < 8) rd(st + kAhead);
+                #pragma unroll
+                for (int c = 0; c < 2; ++c) dW2[c] = mma_bf16(A[st % (kAhead + 1)], B[st % (kAhead + 1)][c], dW2[c]);
+                if (st >> 2 == q) dX = mma_bf16(A[st % (kAhead + 1)], one3, dX);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        __syncthreads();   // B4: h2 rows read
-        #pragma unroll
-        for (int u = 0; u < 4; ++u) stage_row(tB, col_s, 4 * q + u, h, zh[u]);
-        __syncthreads();   // B5: dz2 rows complete
-        // dW2 rows 32g, columns of tiles 2q, 2q + 1 (and db2 through a ones column)
-        #pragma unroll 2
-        for (int st = 0; st < 8; ++st) {
-            const bf16x8 av = tr_operand(tB, 16 * st, 32 * g, lane);
-            #pragma unroll
-            for (int t = 0; t < 2; ++t) dW2[t] = mma_bf16(av, tr_operand(tA, 16 * st, 32 * (2 * q + t), lane), dW2[t]);
-            if (q == 1) dX = mma_bf16(av, ones, dX);
-        }
-        // dh1 = W2^T dz2 on this half's tiles, dz1 = dh1 * relu'(z1), and this
-        // half's share of dL/dfeat = W1[:, :12]^T dz1
-        bf16x8 d1[4];
-        f32x16 dft;
-        #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) dft[rr] = 0.0f;
+        __syncthreads();   // dz1 rows and dL/dfeat shares complete
+        // the sample's record, one 16-byte word per thread of its row
         {
-            bf16x8 zb[8];
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             #pragma unroll
-            for (int st = 0; st < 8; ++st) zb[st] = read_row(tB, col_s, st, h);
-            f32x16 dh1[2];
-            #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) dh1[t][rr] = 0.0f;
-            chain_tiles_plain_bf16<2>(sW2T, lane, 2 * q, zb, dh1);
-            #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                #pragma unroll
-                for (int gg = 0; gg < 2; ++gg) {
-                    const int st = 4 * q + 2 * t + gg;
-                    d1[2 * t + gg] = relu_grad_pack8(dh1[t], gg, read_row(tA, col_s, st, h));
-                    dft = mma_bf16(m < kC ? sW1Tc[(st * 2 + h) * kC + (m < kC ? m : 0)] : zero8, d1[2 * t + gg], dft);
-                }
+            for (int w = 0; w < 4; ++w) {
+                const float4 u = *reinterpret_cast<const float4*>(&sD[w][xrow][xq > 0 ? 4 * (xq - 1) : 0]);
+                v.x += u.x;
+                v.y += u.y;
+                v.z += u.z;
+                v.w += u.w;
+            }
+            v.x = xq > 0 ? v.x : rh.x;
+            v.y = xq > 0 ? v.y : rh.y;
+            v.z = xq > 0 ? v.z : rh.z;
+            v.w = xq > 0 ? v.w : rh.w;
+            if (xrow <= last) a.rec[(static_cast<int64_t>(slot) + cr.y) * 4 + xq] = v;
         }
-        if (q == 1) {
-            if (h == 0) {
-                *reinterpret_cast<float4*>(&sD[col_s][0]) = make_float4(dft[0], dft[1], dft[2], dft[3]);
-                *reinterpret_cast<float4*>(&sD[col_s][8]) = make_float4(dft[4], dft[5], dft[6], dft[7]);
-            } else {
-                *reinterpret_cast<float4*>(&sD[col_s][4]) = make_float4(dft[0], dft[1], dft[2], dft[3]);
+        // dW1's third tile over the half's own dz1 rows
+        if constexpr (KX > 0) {
+            #pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const uint32_t at = trX + ((64 * q + 16 * st) * kXP + 64) * 2;
+                dW1c = mma_bf16(tr_unit(trG + q * (4 * 16 * kH * 2), st),
+                                tr_pair(at, at + 4 * kXP * 2), dW1c);
             }
         }
-        __syncthreads();   // B6: h1 and dz2 rows read; the second half's dL/dfeat in sD
-        // Take delivery of the next block's ray index here, long after its
-        // load: the memory counter that a later wait on it would use also
-        // counts the record stores below, so consuming it at the top of the
-        // next block would wait for those stores to complete.
-        asm volatile("" ::"v"(r_next));
-        #pragma unroll
-        for (int u = 0; u < 4; ++u) stage_row(tA, col_s, 4 * q + u, h, d1[u]);
-        // The sample's record: dft[0..3] hold channels 4h .. 4h + 3 of this
-        // half, dft[4..7] (half 0) channels 8..11: half h writes record word
-        // 1 + h, half 0 also words 0 and 3.  Written with fixed register
-        // indices and one float4 store per word (the two halves' stores
-        // merged into one with a lane-dependent register index had become
-        // 16-way selects and four dword stores).
-        auto write_record = [&]() {
-            if (!ok) return;
-            float4* rec = a.rec + (static_cast<int64_t>(slot0) + cr.y) * 4;
-            const float4 oa = *reinterpret_cast<const float4*>(&sD[col_s][4 * h]);
-            rec[1 + h] = make_float4(dft[0] + oa.x, dft[1] + oa.y, dft[2] + oa.z, dft[3] + oa.w);
-            if (h == 0) {
-                const float4 o8 = *reinterpret_cast<const float4*>(&sD[col_s][8]);
-                rec[0] = rh;
-                rec[3] = make_float4(dft[4] + o8.x, dft[5] + o8.y, dft[6] + o8.z, dft[7] + o8.w);
-            }
-        };
-        if (q == 0) {
-            if constexpr (KX > 0) {
-                // x' = [f, PE_KX(u), PE(d), 1, 0...] -> tB (96 columns, this
-                // lane's half of 24 four-column chunks), the per-sample
-                // inputs evaluated again (every lane, at its clamped
-                // sample).  Their loads go first, then the record (whose
-                // operands then die before the encoding), then the
-                // arithmetic: a wait on those loads does not include the
-                // record stores.
-                SampleIn in;
-                sample_loads<KX>(pa, a.feat, sc, r, in);
-                write_record();
-                float xs[L::kS];
-                sample_encode<KX>(pa, in, xs);
-                const float* per = a.pe + static_cast<int64_t>(r) * 32;
-                auto xval = [&](int j) -> float {
-                    if (j < L::kS) return xs[j < L::kS ? j : 0];
-                    if (j < L::kIn) return per[j - L::kS];
-                    return j == L::kIn ? 1.0f : 0.0f;
-                };
-                constexpr int kChunks = 4 * L::kXT;   // per lane half
-                #pragma unroll
-                for (int kk = 0; kk < kChunks; ++kk) {
-                    bf16x4 bv;
-                    #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        bv[e] = static_cast<__bf16>(h ? xval(4 * (kChunks + kk) + e) : xval(4 * kk + e));
-                    *reinterpret_cast<uint2*>(chunk_at(tB, col_s, kChunks * h + kk)) = __builtin_bit_cast(uint2, bv);
-                }
-            } else {
-                // x' = [f, PE, 1, 0...] -> tB (64 columns, this lane's half of
-                // 8 float4 chunks): half 0 takes f[0..11] and PE[0..19], half 1
-                // PE[20..26] and the constant 1 (stored after the PE) and zeros.
-                // Every lane issues the same unconditional loads; half 1 then
-                // zeroes chunks 2..7.
-                const float4* f4 = reinterpret_cast<const float4*>(a.feat + sc * kC);
-                const float4* p4 = reinterpret_cast<const float4*>(a.pe + static_cast<int64_t>(r) * 32);
-                const float4* c01 = h ? p4 + 5 : f4;
-                float4 v[8] = {c01[0], c01[1], f4[2], p4[0], p4[1], p4[2], p4[3], p4[4]};
-                const uint32_t keep = static_cast<uint32_t>(h) - 1u;   // all ones in half 0, zero in half 1
-                #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    bf16x4 b;
-                    b[0] = static_cast<__bf16>(v[k].x);
-                    b[1] = static_cast<__bf16>(v[k].y);
-                    b[2] = static_cast<__bf16>(v[k].z);
-                    b[3] = static_cast<__bf16>(v[k].w);
-                    uint2 bits = __builtin_bit_cast(uint2, b);
-                    if (k >= 2) {   // a mask, not a branch: both halves run the same code
-                        bits.x &= keep;
-                        bits.y &= keep;
-                    }
-                    *reinterpret_cast<uint2*>(chunk_at(tB, col_s, 8 * h + k)) = bits;
-                }
-                write_record();
+        // ---- dW1 rows 32w, tile q (column kIn: the bias) over the block's samples
+        {
+            constexpr int kAhead = 3;
+            const uint32_t trQ = trX + 64u * q;
+            bf16x8 A[kAhead + 1], B[kAhead + 1];
+            auto rd = [&](int st) {
+                const uint32_t at = trQ + 16 * st * kXP * 2;
+                A[st % (kAhead + 1)] = tr_unit(trG, st);
+                B[st % (kAhead + 1)] = tr_pair(at, at + 4 * kXP * 2);
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            #pragma unroll
+            for (int st = 0; st < kAhead; ++st) rd(st);
+            #pragma unroll
+            for (int st = 0; st < 8; ++st) {
+                load_w(a.w2pb, st);   // W2 for the next block's layer 2
+                if (st + kAhead < 8) rd(st + kAhead);
+                dW1 = mma_bf16(A[st % (kAhead + 1)], B[st % (kAhead + 1)], dW1);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        __syncthreads();   // B7: dz1 and x' rows complete
-        #pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            const bf16x8 av = tr_operand(tA, 16 * st, 32 * g, lane);
-            dW1 = mma_bf16(av, tr_operand(tB, 16 * st, 32 * q, lane), dW1);
-            if (KX > 0 && q == 0) dX = mma_bf16(av, tr_operand(tB, 16 * st, 64, lane), dX);
-        }
-        __builtin_amdgcn_s_waitcnt(0);   // the next block's copies to sPB, sPF have landed
-        __syncthreads();   // B8: rows read before the next block's staging
-        r0 = __builtin_amdgcn_readfirstlane(r0_next);
+        __syncthreads();   // x', sD and sG read before the next block's staging
     }
-    // ---- epilogue: this workgroup's partial of the flat gradient
+    // ---- epilogue: this workgroup's partial of the flat gradient.  Half 1's
+    // sums over its own samples are added to half 0's through LDS.
     float* out = a0.partial + static_cast<int64_t>(blockIdx.x) * L::kPStride;
+    float4* xch = reinterpret_cast<float4*>(sU);   // [2 tiles][4 words][256 threads]
+    static_assert(kZB + kDB >= 2 * 4 * 256 * 16, "the exchange fits sU");
+    const int t4 = t & 255;
     #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-        const int row = 32 * g + acc_row(rr, h);
+    for (int c = 0; c < 3; ++c) db3[c] = wave_total(db3[c]);
+    if (q == 1) {
         #pragma unroll
-        for (int t = 0; t < 2; ++t) out[L::kOffW2 + row * kH + 32 * (2 * q + t) + m] = dW2[t][rr];
-        const int cidx = 32 * q + m;
-        if (cidx < L::kIn) out[L::kOffW1 + row * L::kIn + cidx] = dW1[rr];
-        else if (cidx == L::kIn) out[L::kOffB1 + row] = dW1[rr];
-        if (KX > 0 && q == 0) {
-            const int c2 = 64 + m;
-            if (c2 < L::kIn) out[L::kOffW1 + row * L::kIn + c2] = dX[rr];
-            else if (c2 == L::kIn) out[L::kOffB1 + row] = dX[rr];
+        for (int i = 0; i < 4; ++i) {
+            xch[i * 256 + t4] = make_float4(dX[4 * i], dX[4 * i + 1], dX[4 * i + 2], dX[4 * i + 3]);
+            if (KX > 0) xch[(4 + i) * 256 + t4] = make_float4(dW1c[4 * i], dW1c[4 * i + 1], dW1c[4 * i + 2], dW1c[4 * i + 3]);
         }
-        if (q == 0 && m >= kW3Col && m < kW3Col + 3) out[L::kOffW3 + (m - kW3Col) * kH + row] = dX[rr];
-        if (q == 1 && m == 0) out[L::kOffB2 + row] = dX[rr];
-    }
-    if (q == 0) {
-        #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            db3[t] += __shfl_xor(db3[t], 32, 64);
-            for (int off = 16; off > 0; off >>= 1) db3[t] += __shfl_xor(db3[t], off, 64);
-        }
-        if (lane == 0)
-            for (int t = 0; t < 3; ++t) sRed[g * 4 + t] = db3[t];
+        if (t4 == 0)
+            for (int c = 0; c < 3; ++c) sRed[c] = db3[c];
     }
     __syncthreads();
-    if (threadIdx.x < 3)
-        out[L::kOffB3 + threadIdx.x] = sRed[threadIdx.x] + sRed[4 + threadIdx.x] + sRed[8 + threadIdx.x] +
-                                    sRed[12 + threadIdx.x];
+    #pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = 32 * wave + acc_row(i, h);
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) out[L::kOffW2 + row * kH + 32 * (2 * q + c) + m] = dW2[c][i];
+        const int col = 32 * q + m;
+        if (col < L::kIn) out[L::kOffW1 + row * L::kIn + col] = dW1[i];
+        else if (col == L::kIn) out[L::kOffB1 + row] = dW1[i];
+    }
+    if (q == 1) return;
+    #pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 u = xch[i * 256 + t4];
+        dX[4 * i] += u.x;
+        dX[4 * i + 1] += u.y;
+        dX[4 * i + 2] += u.z;
+        dX[4 * i + 3] += u.w;
+        if (KX > 0) {
+            const float4 v = xch[(4 + i) * 256 + t4];
+            dW1c[4 * i] += v.x;
+            dW1c[4 * i + 1] += v.y;
+            dW1c[4 * i + 2] += v.z;
+            dW1c[4 * i + 3] += v.w;
+        }
+    }
+    #pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = 32 * wave + acc_row(i, h);
+        if (m < 3) out[L::kOffW3 + m * kH + row] = dX[i];
+        else if (m == 3) out[L::kOffB2 + row] = dX[i];
+        if (KX > 0) {
+            const int col = 64 + m;
+            if (col < L::kIn) out[L::kOffW1 + row * L::kIn + col] = dW1c[i];
+            else if (col == L::kIn) out[L::kOffB1 + row] = dW1c[i];
+        }
+    }
+    if (t == 0)
+        for (int c = 0; c < 3; ++c) out[L::kOffB3 + c] = db3[c] + sRed[c];
 }
 
 }  // namespace

@@ -335,47 +335,6 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
 // dW3) and first loads.  390k samples: 328 us, 748 us with float32 matrix
 // instructions.
 // ---------------------------------------------------------------------------
-constexpr int kSB = 64;   // samples per block
-
-// Activation tile of one plane: kSB rows of 16 units of 16 bytes.  Unit
-// 2st + h of a row holds the eight features phi16(st, 0..7, h) that one lane
-// produces and, as the next layer's operand, reads: one 16-byte access each
-// way.  The unit index is permuted by the row, so that eight consecutive rows
-// (one phase of a 16-byte access) and the 4 rows x 2 units of a transpose
-// read's 16 lanes cover all banks.
-__device__ __forceinline__ int unit_swz(int r) { return ((r & 3) << 1) | ((r >> 2) & 1) | (r & 8); }
-
-constexpr int kTile = kSB * kH;             // elements of one plane of an activation tile
-constexpr uint32_t kPlaneB = 2 * kTile;     // its bytes
-constexpr uint32_t kColB = 32 * kH * 2;     // bytes of one column tile's 32 rows
-
-// LDS by byte address, so that one register serves every access that differs
-// by a constant (the instruction's offset field): plane, column tile and K
-// step of an activation tile.
-typedef __attribute__((address_space(3))) char lds_char;
-__device__ __forceinline__ uint32_t lds_addr(void* p) { return (uint32_t)(uintptr_t)(lds_char*)p; }
-template <typename T>
-__device__ __forceinline__ T lds_get(uint32_t a) { return *(__attribute__((address_space(3))) const T*)a; }
-template <typename T>
-__device__ __forceinline__ void lds_put(uint32_t a, const T& v) { *(__attribute__((address_space(3))) T*)a = v; }
-
-// K-major operand from two LDS transpose reads (rows r and r + 4 of a lane's
-// samples): see tr_operand for the lanes' roles.
-__device__ __forceinline__ bf16x8 tr_pair(uint32_t a, uint32_t b) {
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a);
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b);
-    const s16x8 uv = __builtin_shufflevector(u, v, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, uv);
-}
-
-__device__ __forceinline__ f32x16 zero_tile() {
-    f32x16 z;
-    #pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-    return z;
-}
-
 // One lane's 16 values of its tile (accumulator order) as planes into its
 // sample's row: `at` is the address of its first unit, the second is 2 further.
 __device__ __forceinline__ void stage_tile(uint32_t at, const f32x16& v) {

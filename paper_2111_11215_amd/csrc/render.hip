@@ -665,7 +665,7 @@ __global__ __launch_bounds__(kComposeThreads) void compose_step_kernel(ComposeAr
 // ---------------------------------------------------------------------------
 // scatter: transpose of the trilinear gathers, without float atomics.
 // Samples are counting-sorted by fine cell (one integer atomic per run of
-// equal cells in a wavefront), then one thread per grid vertex sums the
+// equal cells in a wavefront), then one lane quad per grid vertex sums the
 // contributions of the samples in its 8 neighbouring cells and adds them to
 // the gradient with a plain read-modify-write.
 // ---------------------------------------------------------------------------
@@ -685,7 +685,6 @@ struct BinArgs {
     int64_t ncell;
 };
 
-
 // Records in binned order when no network backward places them (density
 // only): the head (fractional position, dL/draw) at cell start + rank.
 __global__ __launch_bounds__(256) void bin_place_kernel(BinArgs a) {
@@ -698,81 +697,178 @@ __global__ __launch_bounds__(256) void bin_place_kernel(BinArgs a) {
     }
 }
 
-// Gradient of one vertex (i,j,k): it is corner (dx,dy,dz) of cell
-// (i-dx, j-dy, k-dz); the samples binned in those cells are summed with the
-// vertex's trilinear weight.  acc[0] density, acc[1..12] features.  Returns
-// whether any sample touches the vertex.  For each (dx, dy) the cells k-1
-// (dz = 1) and k (dz = 0) are neighbours in the cell order, so their records
-// form one run, split at the start of cell k; the run is walked two records
-// at a time so that two records' loads are in flight together.
-__device__ __forceinline__ void add_record(const float4* r, int dx, int dy, int dz, bool feat, float acc[13]) {
-    const float4 h = r[0];
-    const float w = (dx ? h.x : 1.0f - h.x) * (dy ? h.y : 1.0f - h.y) * (dz ? h.z : 1.0f - h.z);
-    acc[0] += w * h.w;
-    if (feat) {
-        const float4 q0 = r[1], q1 = r[2], q2 = r[3];
-        acc[1] += w * q0.x; acc[2] += w * q0.y; acc[3] += w * q0.z; acc[4] += w * q0.w;
-        acc[5] += w * q1.x; acc[6] += w * q1.y; acc[7] += w * q1.z; acc[8] += w * q1.w;
-        acc[9] += w * q2.x; acc[10] += w * q2.y; acc[11] += w * q2.z; acc[12] += w * q2.w;
-    }
+// Gradients of a wavefront's 16 consecutive vertices, a lane quad each.  Vertex
+// (i,j,k) is corner (dx,dy,dz) of cell (i-dx, j-dy, k-dz); the samples binned
+// in those cells are summed with the vertex's trilinear weight.  For each
+// (dx,dy) the cells k-1 (dz = 1) and k (dz = 0) are neighbours in the cell
+// order, so their records form one run, split at the start of cell k: lane
+// 2dx + dy of the quad finds it and lists its records in LDS.  Then the quad
+// reads each record as one 64-byte segment (lane `part` its word `part`: the
+// density's, or four features'), kPairsAhead of them in flight.
+//
+// With a vertex per lane, a step of the longest run cost four load
+// instructions with 9 of 64 lanes active: the address units, busy 72 % of the
+// time, bounded the walk.  With the Adam step: 106k samples in 31^3 cells
+// 34 -> 17 us, 153k in 99^3 65 -> 57, 387k in 159^3 183 -> 175, 7.1M in 255^3
+// 1600 -> 1494 (5.7 GB of parameters and moments are 1040 us); the plain
+// gather in 127^3 cells 70 -> 53.  Eight records ahead in fewer wavefronts:
+// 14.5, 58, 191, 1520 us.  Four vertices per quad, their sums through LDS,
+// take fewer loads (7.1M samples 1390 us) but a quarter of the wavefronts: 57
+// us for the first of these.  Sums by LDS float atomics, in any split, were slower than
+// either (64 lanes of one take as many cycles).
+constexpr int kPairs = 32;       // records of a vertex listed at a time
+constexpr int kPairsAhead = 4;
+
+struct PairList {
+    // x: record; y: 1 - (dx, dy, dz) in bytes 0..2
+    uint2 pair[16][kPairs + 1];
+};
+
+// A wavefront's LDS accesses are in order; the compiler is kept from moving them.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ bool vertex_grad(const BinArgs& a, int i, int j, int k, bool feat, float acc[13]) {
-    const int nx = a.g.n[0], cy = a.g.n[1] - 1, cz = a.g.n[2] - 1;
-    #pragma unroll
-    for (int q = 0; q < 13; ++q) acc[q] = 0.0f;
-    // the twelve cell starts first, all in flight together
-    int p0[4], pm[4], p1[4];
-    #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int dx = (c >> 1) & 1, dy = c & 1;
-        const int ci = i - dx, cj = j - dy;
-        p0[c] = pm[c] = p1[c] = 0;
-        if (ci < 0 || cj < 0 || ci >= nx - 1 || cj >= cy) continue;
-        const int row = (ci * cy + cj) * cz;
-        const int klo = k > 0 ? k - 1 : 0, khi = k < cz ? k + 1 : cz;   // cells k-1 and k, where they exist
-        p0[c] = a.cell_start[row + klo];
-        pm[c] = a.cell_start[row + k];
-        p1[c] = a.cell_start[row + khi];
+template <int kPerm>
+__device__ __forceinline__ int quad_bcast(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, kPerm, 0xf, 0xf, true);
+}
+
+struct VertexRun {
+    int p0, pm, p1;   // this lane's run
+};
+
+// Whether any of the quad's lanes has a record.
+__device__ __forceinline__ bool run_touched(const VertexRun& R) {
+    const int any = R.p1 > R.p0;
+    return (quad_bcast<0x00>(any) | quad_bcast<0x55>(any) | quad_bcast<0xaa>(any) | quad_bcast<0xff>(any)) != 0;
+}
+
+// Division of a vertex index by a grid extent, for wavefront-uniform operands
+// (the indices of a grid with its gradients in memory are below 2^32).
+struct GridDivisor {
+    uint32_t d, inv;
+    __device__ explicit GridDivisor(int n) : d(n), inv(0xffffffffu / static_cast<uint32_t>(n)) {}
+    __device__ uint32_t operator()(uint32_t x) const {
+        uint32_t q = static_cast<uint32_t>(static_cast<uint64_t>(x) * inv >> 32);   // one or two too small
+        q += x - q * d >= d;
+        return q + (x - q * d >= d);
     }
-    bool any = false;
-    #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int dx = (c >> 1) & 1, dy = c & 1;
-        int p = p0[c];
-        for (; p + 1 < p1[c]; p += 2) {
-            add_record(a.rec + static_cast<int64_t>(p) * 4, dx, dy, p < pm[c], feat, acc);
-            add_record(a.rec + static_cast<int64_t>(p + 1) * 4, dx, dy, p + 1 < pm[c], feat, acc);
+};
+
+// v0: the wavefront's first vertex (uniform); vertices beyond nv have no runs.
+__device__ __forceinline__ VertexRun vertex_run(const BinArgs& a, GridDivisor by_nz, GridDivisor by_ny, uint32_t v0,
+                                                int64_t nv) {
+    const int lane = threadIdx.x & 63, c = lane & 3;
+    const int nx = a.g.n[0], ny = a.g.n[1], nz = a.g.n[2], cy = ny - 1, cz = nz - 1;
+    const uint32_t line = by_nz(v0);
+    int i = static_cast<int>(by_ny(line)), j = static_cast<int>(line - i * static_cast<uint32_t>(ny));
+    int k = static_cast<int>(v0 - line * static_cast<uint32_t>(nz)) + (lane >> 2);
+    while (k >= nz) {   // at most 16 / nz times
+        k -= nz;
+        if (++j == ny) {
+            j = 0;
+            ++i;
         }
-        if (p < p1[c]) add_record(a.rec + static_cast<int64_t>(p) * 4, dx, dy, p < pm[c], feat, acc);
-        any |= p1[c] > p0[c];
     }
-    return any;
+    const int ci = i - (c >> 1), cj = j - (c & 1);
+    VertexRun R;
+    R.p0 = R.pm = R.p1 = 0;
+    if (v0 + static_cast<int64_t>(lane >> 2) < nv && ci >= 0 && cj >= 0 && ci < nx - 1 && cj < cy) {
+        const int row = (ci * cy + cj) * cz;
+        R.p0 = a.cell_start[row + max(k - 1, 0)];   // cells k-1 and k, where they exist
+        R.pm = a.cell_start[row + k];
+        R.p1 = a.cell_start[row + min(k + 1, cz)];
+    }
+    return R;
 }
 
-// One thread per vertex: add its gradient into the gradient grids.
+// The whole wavefront calls this: word `part` of the quad's vertex's sums
+// (part 0: density in .w).
+__device__ __forceinline__ float4 vertex_sum(const BinArgs& a, VertexRun R, PairList& S) {
+    const int lane = threadIdx.x & 63, part = lane & 3;
+    uint2* list = S.pair[lane >> 2];
+    const uint32_t y0 = (1u - (part >> 1)) | (1u - (part & 1)) << 8 | 1u << 16, y1 = y0 & 0xffffu;
+    const float4* rec = a.rec + part;
+    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    bool more = R.p1 > R.p0;
+    while (__any(more)) {
+        // this lane's records, after those of the lanes before it
+        const int n = min(R.p1 - R.p0, kPairs);
+        const int n0 = quad_bcast<0x00>(n), n1 = quad_bcast<0x55>(n), n2 = quad_bcast<0xaa>(n),
+                  n3 = quad_bcast<0xff>(n);
+        const int at = (part > 0 ? n0 : 0) + (part > 1 ? n1 : 0) + (part > 2 ? n2 : 0);
+        const int total = min(n0 + n1 + n2 + n3, kPairs);
+        const int take = max(min(n, kPairs - at), 0);
+        wave_lds_fence();   // the list's last readers are done
+        for (int i = 0; i < take; ++i)
+            list[at + i] = make_uint2(static_cast<uint32_t>(R.p0 + i), R.p0 + i < R.pm ? y1 : y0);
+        R.p0 += take;
+        more = R.p1 > R.p0;
+        wave_lds_fence();
+        // (no branch per record: the loads are to be in flight together)
+        for (int b = 0; b < total; b += kPairsAhead) {
+            uint32_t y[kPairsAhead];
+            float4 r[kPairsAhead];
+            const bool all = __any(b + kPairsAhead / 2 < total);
+            #pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                if (half && !all) break;
+                #pragma unroll
+                for (int u = half * kPairsAhead / 2; u < (half + 1) * kPairsAhead / 2; ++u) {
+                    const uint2 x = list[min(b + u, total - 1)];
+                    y[u] = x.y;
+                    r[u] = rec[static_cast<uint64_t>(x.x) * 4];
+                }
+            }
+            #pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                if (half && !all) break;
+                #pragma unroll
+                for (int u = half * kPairsAhead / 2; u < (half + 1) * kPairsAhead / 2; ++u) {
+                    // dx ? fx : 1 - fx as |fx - (1 - dx)| (the position in the cell is in [0, 1])
+                    const float w0 = fabsf(r[u].x - static_cast<float>(y[u] & 255u)) *
+                                     fabsf(r[u].y - static_cast<float>(y[u] >> 8 & 255u)) *
+                                     fabsf(r[u].z - static_cast<float>(y[u] >> 16 & 255u));
+                    const int wb = b + u < total ? __float_as_int(w0) : 0;
+                    const float w = __int_as_float(quad_bcast<0x00>(wb));   // lane 0 holds the head
+                    acc.x += w * r[u].x;
+                    acc.y += w * r[u].y;
+                    acc.z += w * r[u].z;
+                    acc.w += w * r[u].w;
+                }
+            }
+        }
+    }
+    return acc;
+}
+
+// Adds the vertices' gradients into the gradient grids.
 __global__ __launch_bounds__(256) void vertex_gather_kernel(BinArgs a) {
-    const int ny = a.g.n[1], nz = a.g.n[2];
-    const int64_t nv = static_cast<int64_t>(a.g.n[0]) * ny * nz;
-    const bool feat = a.with_feat != 0;
-    for (int64_t v = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; v < nv;
-         v += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int k = static_cast<int>(v % nz);
-        const int j = static_cast<int>((v / nz) % ny);
-        const int i = static_cast<int>(v / (static_cast<int64_t>(nz) * ny));
-        float acc[13];
-        const bool any = vertex_grad(a, i, j, k, feat, acc);
-        if (!any) continue;
-        a.grad_density[v] += acc[0];
-        if (feat) {
-            float4* gf = reinterpret_cast<float4*>(a.grad_feat + v * kC);
-            float4 g0 = gf[0], g1 = gf[1], g2 = gf[2];
-            g0.x += acc[1]; g0.y += acc[2]; g0.z += acc[3]; g0.w += acc[4];
-            g1.x += acc[5]; g1.y += acc[6]; g1.z += acc[7]; g1.w += acc[8];
-            g2.x += acc[9]; g2.y += acc[10]; g2.z += acc[11]; g2.w += acc[12];
-            gf[0] = g0;
-            gf[1] = g1;
-            gf[2] = g2;
+    __shared__ PairList lists[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane & 3;
+    const int64_t nv = static_cast<int64_t>(a.g.n[0]) * a.g.n[1] * a.g.n[2];
+    const GridDivisor by_nz(a.g.n[2]), by_ny(a.g.n[1]);
+    for (int64_t v0 = static_cast<int64_t>(blockIdx.x) * 64 + 16 * wave; v0 < nv;
+         v0 += static_cast<int64_t>(gridDim.x) * 64) {
+        const VertexRun R = vertex_run(a, by_nz, by_ny, static_cast<uint32_t>(v0), nv);
+        const bool touched = run_touched(R);
+        if (!__any(touched)) continue;
+        const float4 g = vertex_sum(a, R, lists[wave]);
+        if (!touched) continue;
+        const int64_t v = v0 + (lane >> 2);
+        if (part == 0) {
+            a.grad_density[v] += g.w;
+        } else if (a.with_feat) {
+            float4* gf = reinterpret_cast<float4*>(a.grad_feat + v * kC) + part - 1;
+            float4 o = *gf;
+            o.x += g.x;
+            o.y += g.y;
+            o.z += g.z;
+            o.w += g.w;
+            *gf = o;
         }
     }
 }
@@ -790,13 +886,11 @@ struct GridAdamArgs {
     dvgo::AdamCoef c;
 };
 
-// One thread per vertex: its gradient as in vertex_gather_kernel, then the
-// Adam step of its density and its 12 features (and their bfloat16 copy);
-// a vertex no sample touches takes the step with a zero gradient, as dense
-// Adam does.  The gradient never reaches memory.  Feature streams are
-// walked in wave-contiguous float4 chunks (the 64 vertices of a wave own
-// 768 consecutive values): the wave's gradients go through LDS so that every
-// load and store of p, m, v and the copy covers whole cache lines.
+// The vertices' gradients as in vertex_gather_kernel, then the Adam step of
+// their densities and features (and their bfloat16 copy), each lane on the
+// values it has summed; a vertex no sample touches takes the step with a zero
+// gradient, as dense Adam does.  The gradient never reaches memory.  A
+// wavefront's 16 vertices own 768 consecutive bytes of each feature stream.
 //
 // With an activity mask, a vertex whose bit is clear (both moments zero)
 // and that no sample touches is skipped: its step would compute m = v = 0
@@ -804,8 +898,9 @@ struct GridAdamArgs {
 // parameters and moments are neither read nor written.  A vertex that takes
 // a step with any non-zero gradient gets its bit set.
 __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAdamArgs& o, int blk, int nblk) {
-    __shared__ float4 sg[4][64 * 3];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ PairList lists[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int vl = lane >> 2, part = lane & 3;
     const int ny = a.g.n[1], nz = a.g.n[2];
     const int64_t nv = static_cast<int64_t>(a.g.n[0]) * ny * nz;
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -813,7 +908,8 @@ __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAda
     f4* P = reinterpret_cast<f4*>(o.pf);
     f4* M = reinterpret_cast<f4*>(o.mf);
     f4* V = reinterpret_cast<f4*>(o.vf);
-    u2* S = reinterpret_cast<u2*>(o.shadow);
+    u2* shadow = reinterpret_cast<u2*>(o.shadow);
+    uint16_t* active = reinterpret_cast<uint16_t*>(o.active);   // a wavefront's 16 bits
     // Workgroups are dealt to the 8 XCDs round robin (block b on XCD b % 8).
     // The vertices are cut into chunks of two x-planes (rounded up to a
     // multiple of 256), dealt to the XCDs round robin as well: a cell's
@@ -821,125 +917,104 @@ __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAda
     // x-planes, which then mostly sit in one chunk and so in one XCD's L2,
     // and every XCD gets an even share of the grid's busy middle (its
     // vertices with moments and samples) and of its idle rim.  The blocks of
-    // an XCD walk its chunks in 256-vertex steps.  gridDim.x is a multiple of
-    // 8; every wave's first vertex is a multiple of 64, so a wave owns two
-    // whole words of the activity mask.
+    // an XCD walk its chunks in 64-vertex steps.  gridDim.x is a multiple of
+    // 8; every wave's first vertex is a multiple of 16, so a wave owns a
+    // half word of the activity mask.
     const int64_t kChunk = (2 * static_cast<int64_t>(ny) * nz + 255) / 256 * 256;
     const int xcd = blk & 7, nloc = nblk >> 3, loc = blk >> 3;
     const int64_t nchunk = (nv + kChunk - 1) / kChunk;
     const int64_t mine = nchunk > xcd ? (nchunk - xcd + 7) / 8 : 0;   // chunks of this XCD
-    const int64_t hi = nv;
-    for (int64_t l = static_cast<int64_t>(loc) * blockDim.x; l < mine * kChunk;
-         l += static_cast<int64_t>(nloc) * blockDim.x) {
-        const int64_t base = ((l / kChunk) * 8 + xcd) * kChunk + l % kChunk;   // increases with l
-        if (base >= hi) break;
-        const int64_t v = base + threadIdx.x;
-        const int64_t vbase = base + 64 * wave;
-        const int64_t nwave = hi - vbase < 64 ? hi - vbase : 64;   // vertices of this wave (may be <= 0)
-        const bool in = v < hi;
-        const bool was_active = in && (!o.active || ((o.active[v >> 5] >> (v & 31)) & 1u));
-        // issue the parameter streams of the active vertices first: they do
-        // not depend on the gradient and overlap the latency of the sample
-        // gather below
-        const uint64_t act_mask = __ballot(was_active);
-        float p = 0.0f, m = 0.0f, w = 0.0f;
-        if (was_active) {
-            p = __builtin_nontemporal_load(o.pd + v);
-            m = __builtin_nontemporal_load(o.md + v);
-            w = __builtin_nontemporal_load(o.vd + v);
+    const GridDivisor by_nz(nz), by_ny(ny);
+    int64_t chunk = 0, in_chunk = static_cast<int64_t>(loc) * 64;
+    // the wave's first vertex of each step (nv: none left), increasing
+    auto first_vertex = [&]() -> int64_t {
+        while (in_chunk >= kChunk) {
+            in_chunk -= kChunk;
+            ++chunk;
         }
-        f4 pq[3], mq[3], vq[3];
-        #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int c = 64 * q + lane;
-            if (c < 3 * nwave && ((act_mask >> (c / 3)) & 1u)) {
-                const int64_t gi = 3 * vbase + c;
-                pq[q] = __builtin_nontemporal_load(P + gi);
-                mq[q] = __builtin_nontemporal_load(M + gi);
-                vq[q] = __builtin_nontemporal_load(V + gi);
-            }
-        }
-        float acc[13];
-        #pragma unroll
-        for (int q = 0; q < 13; ++q) acc[q] = 0.0f;
-        bool touched = false;
-        if (in && a.cell_start) {   // else no samples in the batch
-            const int k = static_cast<int>(v % nz);
-            const int j = static_cast<int>((v / nz) % ny);
-            const int i = static_cast<int>(v / (static_cast<int64_t>(nz) * ny));
-            touched = vertex_grad(a, i, j, k, true, acc);
-        }
-        // vertices newly reached by a sample: their streams now
+        const int64_t v0 = (chunk * 8 + xcd) * kChunk + in_chunk + 16 * wave;
+        in_chunk += static_cast<int64_t>(nloc) * 64;
+        return chunk < mine && v0 < nv ? v0 : nv;
+    };
+    // a step's runs and activity bits are loaded a step ahead
+    VertexRun ahead;
+    uint32_t bits_ahead = 0xffffu;
+    auto load_ahead = [&](int64_t v0) {
+        ahead.p0 = ahead.pm = ahead.p1 = 0;
+        if (v0 >= nv) return;
+        if (a.cell_start) ahead = vertex_run(a, by_nz, by_ny, static_cast<uint32_t>(v0), nv);   // else no samples
+        if (active) bits_ahead = active[v0 >> 4];
+    };
+    int64_t next = first_vertex();
+    load_ahead(next);
+    while (next < nv) {
+        const int64_t v0 = next;
+        const int64_t v = v0 + vl;
+        const VertexRun R = ahead;
+        const uint32_t was = bits_ahead;
+        const bool was_active = v < nv && ((was >> vl) & 1u);
+        const bool touched = run_touched(R);
         const bool need = was_active || touched;
-        const uint64_t need_mask = __ballot(need);
-        const uint64_t late_mask = need_mask & ~act_mask;
-        if (need && !was_active) {
-            p = __builtin_nontemporal_load(o.pd + v);
-            m = __builtin_nontemporal_load(o.md + v);
-            w = __builtin_nontemporal_load(o.vd + v);
-        }
-        if (late_mask) {
-            #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int c = 64 * q + lane;
-                if (c < 3 * nwave && ((late_mask >> (c / 3)) & 1u)) {
-                    const int64_t gi = 3 * vbase + c;
-                    pq[q] = __builtin_nontemporal_load(P + gi);
-                    mq[q] = __builtin_nontemporal_load(M + gi);
-                    vq[q] = __builtin_nontemporal_load(V + gi);
-                }
+        next = first_vertex();
+        load_ahead(next);
+        if (!__any(need)) continue;
+        // the parameters' streams, in flight while the records are summed
+        f4 pq, mq, vq;
+        if (need) {
+            if (part) {
+                const int64_t at = 3 * v + part - 1;
+                pq = __builtin_nontemporal_load(P + at);
+                mq = __builtin_nontemporal_load(M + at);
+                vq = __builtin_nontemporal_load(V + at);
+            } else {
+                pq[3] = __builtin_nontemporal_load(o.pd + v);
+                mq[3] = __builtin_nontemporal_load(o.md + v);
+                vq[3] = __builtin_nontemporal_load(o.vd + v);
             }
         }
+        float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (__any(touched)) g = vertex_sum(a, R, lists[wave]);
+        const float gg[4] = {g.x, g.y, g.z, g.w};
         if (need) {
-            dvgo::adam_update(o.c, p, acc[0], m, w);
-            __builtin_nontemporal_store(p, o.pd + v);
-            __builtin_nontemporal_store(m, o.md + v);
-            __builtin_nontemporal_store(w, o.vd + v);
-        }
-        #pragma unroll
-        for (int q = 0; q < 3; ++q)
-            sg[wave][3 * lane + q] = make_float4(acc[1 + 4 * q], acc[2 + 4 * q], acc[3 + 4 * q], acc[4 + 4 * q]);
-        __syncthreads();
-        #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int c = 64 * q + lane;
-            if (c < 3 * nwave && ((need_mask >> (c / 3)) & 1u)) {
-                const int64_t gi = 3 * vbase + c;
-                const float4 g = sg[wave][c];
-                const float gg[4] = {g.x, g.y, g.z, g.w};
-                #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float pe = pq[q][e], me = mq[q][e], ve = vq[q][e];
-                    dvgo::adam_update(o.c, pe, gg[e], me, ve);
-                    pq[q][e] = pe;
-                    mq[q][e] = me;
-                    vq[q][e] = ve;
-                }
-                __builtin_nontemporal_store(pq[q], P + gi);
-                __builtin_nontemporal_store(mq[q], M + gi);
-                __builtin_nontemporal_store(vq[q], V + gi);
-                if (S) {
-                    const uint2 b = dvgo::bf16x4_bits(make_float4(pq[q].x, pq[q].y, pq[q].z, pq[q].w));
+            #pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float pe = pq[e], me = mq[e], ve = vq[e];
+                dvgo::adam_update(o.c, pe, gg[e], me, ve);
+                pq[e] = pe;
+                mq[e] = me;
+                vq[e] = ve;
+            }
+            if (part) {
+                const int64_t at = 3 * v + part - 1;
+                __builtin_nontemporal_store(pq, P + at);
+                __builtin_nontemporal_store(mq, M + at);
+                __builtin_nontemporal_store(vq, V + at);
+                if (shadow) {
+                    const uint2 b = dvgo::bf16x4_result(make_float4(pq.x, pq.y, pq.z, pq.w));
                     u2 bv;
                     bv.x = b.x;
                     bv.y = b.y;
-                    __builtin_nontemporal_store(bv, S + gi);
+                    __builtin_nontemporal_store(bv, shadow + at);
                 }
+            } else {
+                __builtin_nontemporal_store(pq[3], o.pd + v);
+                __builtin_nontemporal_store(mq[3], o.md + v);
+                __builtin_nontemporal_store(vq[3], o.vd + v);
             }
         }
-        if (o.active) {
-            bool nonzero = false;
+        if (active && __any(touched)) {   // (bits are only ever set)
+            const int nonzero = touched && (g.w != 0.0f || (part && (g.x != 0.0f || g.y != 0.0f || g.z != 0.0f)));
+            const uint64_t now = __ballot(quad_bcast<0x00>(nonzero) | quad_bcast<0x55>(nonzero) |
+                                          quad_bcast<0xaa>(nonzero) | quad_bcast<0xff>(nonzero));
+            uint32_t bits = 0;   // the quads' bits, gathered to one half word
             #pragma unroll
-            for (int q = 0; q < 13; ++q) nonzero |= acc[q] != 0.0f;
-            const uint64_t now = __ballot(was_active || (touched && nonzero));
-            if (lane == 0 && nwave > 0) o.active[vbase >> 5] = static_cast<uint32_t>(now);
-            if (lane == 1 && nwave > 32) o.active[(vbase >> 5) + 1] = static_cast<uint32_t>(now >> 32);
+            for (int q = 0; q < 16; ++q) bits |= static_cast<uint32_t>(now >> (4 * q) & 1u) << q;
+            if (bits & ~was && lane == 0) active[v0 >> 4] = static_cast<uint16_t>(was | bits);
         }
-        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(256) void vertex_adam_kernel(BinArgs a, GridAdamArgs o) {
+__global__ __launch_bounds__(256, 6) void vertex_adam_kernel(BinArgs a, GridAdamArgs o) {
     vertex_adam_body(a, o, blockIdx.x, gridDim.x);
 }
 
@@ -1069,7 +1144,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceArgs R) { re
 // The fused grid Adam and the reduction of the network's gradient partials
 // in one launch (independent of each other): the first vblocks workgroups
 // step the grids, the rest reduce, filling the grid step's tail.
-__global__ __launch_bounds__(256) void vertex_adam_reduce_kernel(BinArgs a, GridAdamArgs o, int vblocks,
+__global__ __launch_bounds__(256, 6) void vertex_adam_reduce_kernel(BinArgs a, GridAdamArgs o, int vblocks,
                                                                  ReduceArgs R) {
     const int blk = static_cast<int>(blockIdx.x);
     if (blk < vblocks) vertex_adam_body(a, o, blk, vblocks);
@@ -1147,11 +1222,11 @@ int32_t grid_adam_args(const dvgo_grid_adam* opt, GridAdamArgs* o) {
 }
 
 // Workgroups of the fused grid Adam: a multiple of 8 (one share per XCD),
-// 4 per compute unit (its register use allows 4 wavefronts per SIMD; more
-// resident workgroups measured slower), no more than the vertices need.
+// 6 per compute unit (as many as its registers let be resident), no more than
+// the vertices need.
 int grid_adam_blocks(int64_t nv) {
-    const int64_t per_xcd = (nv + 8 * 256 - 1) / (8 * 256);
-    int64_t b = static_cast<int64_t>(dvgo::device_cu_count()) * 4 / 8;
+    const int64_t per_xcd = (nv + 8 * 64 - 1) / (8 * 64);
+    int64_t b = static_cast<int64_t>(dvgo::device_cu_count()) * 6 / 8;
     if (b > per_xcd) b = per_xcd;
     if (b < 1) b = 1;
     return static_cast<int>(8 * b);
@@ -1399,7 +1474,7 @@ int32_t run_vertex(const Common& cm, const dvgo_field* field, const Bins& b, boo
     } else if (opt)
         DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_kernel, dim3(grid_adam_blocks(nv)), dim3(256), 0, s, ba, *opt);
     else
-        DVGO_LAUNCH(K_SCATTER, vertex_gather_kernel, dim3(grid_for(nv, 256, cus * 16)), dim3(256), 0, s, ba);
+        DVGO_LAUNCH(K_SCATTER, vertex_gather_kernel, dim3(grid_for(nv, 64, cus * 16)), dim3(256), 0, s, ba);
     return dvgo::launch_status();
 }
 

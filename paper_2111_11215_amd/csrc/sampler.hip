@@ -266,7 +266,8 @@ __device__ __forceinline__ int wave_incl_scan_int(int v, int lane) {
     return v + (row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
 }
 
-// Single-workgroup exclusive scan: ray_offset[i] = sum_{j<i} counts[j].  The
+// Single-workgroup exclusive scan (beyond kGroupedMaxRays, and no rays):
+// ray_offset[i] = sum_{j<i} counts[j].  The
 // total is below 2^31 (the host bounds B * max_samples), so the scan runs in
 // 32-bit integers.  Each thread takes kPer consecutive counts, so one pass
 // covers kScanThreads * kPer = 8192 rays.
@@ -371,22 +372,49 @@ __global__ __launch_bounds__(256) void fill_kept_kernel(KeepArgs a, const int* _
     fill_ray(a, v, ray_offset[slot], capacity, sample_ray, sample_k, lane);
 }
 
-// Ray offsets and the kept pairs in one launch, for batches of at most
-// kFusedMaxRays rays.  A workgroup takes kFillRays consecutive ray slots, one
-// per wavefront.  It sums the counts of every slot before its first (at most
-// kFusedMaxRays / 1024 loads per thread, all issued before the sum), adds the
-// counts of the slots before each wavefront's own, writes the slots' offsets
-// (the workgroup holding the last slot also writes ray_offset[B] and n_kept)
-// and fills.  Integer sums, so every offset equals the scan's.
+// Ray offsets and the kept pairs in one launch.  A workgroup takes kFillRays
+// consecutive ray slots, one per wavefront.  It sums the counts of every slot
+// before its first, adds the counts of the slots before each wavefront's own,
+// writes the slots' offsets (the workgroup holding the last slot also writes
+// ray_offset[B] and n_kept) and fills.  Integer sums, so every offset equals
+// the scan's.  Up to kFusedMaxRays rays the counts themselves are summed (at
+// most kFusedMaxRays / 1024 loads per thread, all issued before the sum); up
+// to kGroupedMaxRays the sums of the kGroup-ray groups before the workgroup's
+// own (group_sums_kernel: one load per thread) and the counts of its group.
+// The scan by a single workgroup in their place and the fill took 35 + 17 us
+// of 65536 rays, 18 + 18 of 32768; the groups' sums and this kernel take 5 +
+// 22 and 4 + 21.  Beyond kGroupedMaxRays a workgroup would have several loads
+// per thread to make for its 16 rays.
 constexpr int kFillRays = 16;
 constexpr int kFusedMaxRays = 16384;
+constexpr int kGroup = 1024;
+constexpr int kGroupedMaxRays = 1024 * kGroup;
 
+__global__ __launch_bounds__(256) void group_sums_kernel(const int* __restrict__ counts, int B,
+                                                         int* __restrict__ groups) {
+    __shared__ int part[4];
+    const int first = blockIdx.x * kGroup, tid = threadIdx.x;
+    int v = 0;
+    #pragma unroll
+    for (int u = 0; u < kGroup / 256; ++u) {
+        const int i = first + 256 * u + tid;
+        v += i < B ? counts[i] : 0;
+    }
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = v;
+    __syncthreads();
+    if (tid == 0) groups[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+template <bool kGroups>
 __global__ __launch_bounds__(1024) void offsets_fill_kernel(KeepArgs a, const int* __restrict__ counts,
+                                                            const int* __restrict__ groups,
                                                             int* __restrict__ ray_offset,
                                                             int64_t* __restrict__ n_kept, int64_t capacity,
                                                             int* __restrict__ sample_ray,
                                                             int* __restrict__ sample_k) {
-    constexpr int kLoads = kFusedMaxRays / 1024;
+    constexpr int kLoads = kGroups ? 1 : kFusedMaxRays / 1024;
+    static_assert(kGroup == 1024 && kGroupedMaxRays / kGroup <= 1024 && kGroup % kFillRays == 0, "one load each");
     __shared__ int wpart[16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -395,19 +423,22 @@ __global__ __launch_bounds__(1024) void offsets_fill_kernel(KeepArgs a, const in
     // counts of this workgroup's slots (lanes 0..15; clamped, masked below)
     const int own_i = first + (lane & (kFillRays - 1));
     const int own = counts[own_i < a.B ? own_i : a.B - 1];
-    // counts of all slots before the workgroup's first
+    // counts of all slots before the workgroup's first, from slot `from` on
+    // one by one
+    const int from = kGroups ? first / kGroup * kGroup : 0;
+    int part = 0;
+    if (kGroups && tid < first / kGroup) part = groups[tid];
     int c[kLoads];
     #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
         c[u] = 0;
-        if (1024 * u < first) {   // workgroup-uniform
-            const int i = tid + 1024 * u;
+        if (from + 1024 * u < first) {   // workgroup-uniform
+            const int i = from + tid + 1024 * u;
             c[u] = counts[i < first ? i : first - 1];
         }
     }
-    int part = 0;
     #pragma unroll
-    for (int u = 0; u < kLoads; ++u) part += tid + 1024 * u < first ? c[u] : 0;
+    for (int u = 0; u < kLoads; ++u) part += from + tid + 1024 * u < first ? c[u] : 0;
     // workgroup sum: row scans, then the rows' totals, then the wavefronts'
     part += __builtin_amdgcn_update_dpp(0, part, 0x111, 0xf, 0xf, true);
     part += __builtin_amdgcn_update_dpp(0, part, 0x112, 0xf, 0xf, true);
@@ -621,9 +652,18 @@ static int32_t sample_rays_impl(const float* rays_o, const float* rays_d, const 
         DVGO_LAUNCH(K_COUNT_KEPT, count_kept_kernel, dim3(wblocks), dim3(256), 0, s, ka, counts);
         if (int32_t st = dvgo::launch_status()) return st;
     }
+    const dim3 fill((B + kFillRays - 1) / kFillRays);
     if (B <= kFusedMaxRays) {
-        DVGO_LAUNCH(K_FILL_KEPT, offsets_fill_kernel, dim3((B + kFillRays - 1) / kFillRays), dim3(1024), 0, s, ka,
-                    counts, ray_offset, n_kept, capacity, sample_ray, sample_k);
+        DVGO_LAUNCH(K_FILL_KEPT, offsets_fill_kernel<false>, fill, dim3(1024), 0, s, ka, counts,
+                    static_cast<const int*>(nullptr), ray_offset, n_kept, capacity, sample_ray, sample_k);
+        return dvgo::launch_status();
+    }
+    if (B <= kGroupedMaxRays) {
+        int* groups = reinterpret_cast<int*>(keys);   // (the Morton order has been read from them)
+        DVGO_LAUNCH(K_SCAN, group_sums_kernel, dim3((B + kGroup - 1) / kGroup), dim3(256), 0, s, counts, B, groups);
+        if (int32_t st = dvgo::launch_status()) return st;
+        DVGO_LAUNCH(K_FILL_KEPT, offsets_fill_kernel<true>, fill, dim3(1024), 0, s, ka, counts, groups, ray_offset,
+                    n_kept, capacity, sample_ray, sample_k);
         return dvgo::launch_status();
     }
     DVGO_LAUNCH(K_SCAN, scan_offsets_kernel, dim3(1), dim3(kScanThreads), 0, s, counts, B, ray_offset, n_kept);

@@ -447,13 +447,22 @@ __device__ __forceinline__ int cell_of(const GridArgs& g, const float x[3], floa
     return (i0[0] * (g.n[1] - 1) + i0[1]) * (g.n[2] - 1) + i0[2];
 }
 
+// What the fused adjoint takes over from the forward of its ray: per sample of
+// the first kKeptSteps 64-sample steps w_k and the inclusive sum of
+// sigma*delta in its step (each lane reads what it wrote), log T at the start
+// of step j in lane j (steps below 64), dL/dC and log T_end.  4 KB per
+// wavefront, so that 32 of them share a compute unit.
+constexpr int kKeptSteps = 8;
+struct KeptRay {
+    float2* kept;   // [kKeptSteps][64]
+    float start, g[3], log_t_end;
+};
+
 // Forward compositing of ray slot `slot` by one wavefront (segs: its 32
 // segment sums in LDS).  With a.target it also forms the photometric
-// gradient dL/dC; every lane returns that gradient in g and log T_end in
-// *log_t_end (what a fused adjoint needs).
-template <bool kInline>   // kInline: the raw densities interpolated here (a.density_in)
-__device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, int lane, float* segs, float g[3],
-                                                float* log_t_end) {
+// gradient dL/dC; every lane returns that gradient and log T_end in K.
+template <bool kInline, bool kKeep>   // kInline: the raw densities interpolated here (a.density_in)
+__device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, int lane, float* segs, KeptRay& K) {
     const int64_t n = live_count(a.n_kept, a.cap);
     const int r = a.perm[slot];
     int64_t s0 = a.ray_offset[slot], s1 = a.ray_offset[slot + 1];
@@ -508,6 +517,11 @@ __device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, 
         const float incl = wave_incl_scan(sd, lane);
         const float excl = dpp_wave<0x138>(incl);   // wave_shr:1, lane 0 reads 0
         const float w = ok ? expf(logT - excl) * alpha : 0.0f;
+        if constexpr (kKeep) {
+            const int64_t it = (base - s0) >> 6;
+            if (lane == it) K.start = logT;
+            if (it < kKeptSteps) K.kept[it * 64 + lane] = make_float2(w, incl);
+        }
         cr += w * c0; cg += w * c1; cb += w * c2;
         dep += w * tk;
         accw += w;
@@ -526,8 +540,8 @@ __device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, 
     __builtin_amdgcn_wave_barrier();
     // the ray's colour and loss terms, in every lane (the stores from lane 0)
     const float T = expf(logT);
-    g[0] = g[1] = g[2] = 0.0f;
-    *log_t_end = logT;
+    K.g[0] = K.g[1] = K.g[2] = 0.0f;
+    K.log_t_end = logT;
     if (a.rgb) {
         const float c3[3] = {cr + T * a.bg[0], cg + T * a.bg[1], cb + T * a.bg[2]};
         if (lane == 0) {
@@ -540,7 +554,7 @@ __device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, 
             float e2 = 0.0f;
             for (int c = 0; c < 3; ++c) {
                 const float d = c3[c] - a.target[3 * r + c];
-                g[c] = 2.0f * d * invB;
+                K.g[c] = 2.0f * d * invB;
                 e2 += d * d;
             }
             if (a.w_pt > 0.0f) e2 += a.w_pt * ptl;
@@ -549,7 +563,7 @@ __device__ __forceinline__ void compose_fwd_ray(const ComposeArgs& a, int slot, 
                 e2 += a.w_bg * (-pb * logf(pb) - (1.0f - pb) * log1pf(-pb));
             }
             if (lane == 0) {
-                for (int c = 0; c < 3; ++c) a.grad_rgb_out[3 * r + c] = g[c];
+                for (int c = 0; c < 3; ++c) a.grad_rgb_out[3 * r + c] = K.g[c];
                 a.sq_err[r] = e2;
             }
         }
@@ -576,8 +590,8 @@ __global__ __launch_bounds__(kComposeThreads) void compose_fwd_kernel(ComposeArg
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int slot = blockIdx.x * kComposeWaves + wave;
     if (slot >= a.B) return;
-    float g[3], lt;
-    compose_fwd_ray<kInline>(a, slot, lane, segs[wave], g, &lt);
+    KeptRay K;
+    compose_fwd_ray<kInline, false>(a, slot, lane, segs[wave], K);
 }
 
 // Backward of compose: walk each ray from its end in 64-sample steps,
@@ -593,11 +607,12 @@ __device__ __forceinline__ float sd_of(const ComposeArgs& a, int64_t s, int64_t 
     return s < s1 ? softplus_f(a.raw[s] + a.act_shift) * a.sa.step : 0.0f;
 }
 
-// The adjoint of ray slot `slot` by one wavefront.  gin (dL/dC) and
-// log_t_end come from the fused forward's registers, or (gin NULL) from
-// a.grad_rgb and a.log_t_end_in.
-__device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, int lane, const float* gin,
-                                                float log_t_end) {
+// The adjoint of ray slot `slot` by one wavefront.  kFused: with what the
+// forward has kept in K (no depth or opacity gradient then), else from
+// a.grad_* and a.log_t_end_in.
+template <bool kFused>
+__device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, int lane, const KeptRay& K) {
+    constexpr int kCh = kFused ? 3 : 5;   // channels: colour; depth and opacity
     const int64_t n = live_count(a.n_kept, a.cap);
     const int r = a.perm[slot];
     int64_t s0 = a.ray_offset[slot], s1 = a.ray_offset[slot + 1];
@@ -610,11 +625,9 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
     const float p = a.sa.jitter ? a.sa.jitter[r] : 0.0f;
     const float step = a.sa.step;
     float g[5];
-    g[0] = gin ? gin[0] : a.grad_rgb ? a.grad_rgb[3 * r + 0] : 0.0f;
-    g[1] = gin ? gin[1] : a.grad_rgb ? a.grad_rgb[3 * r + 1] : 0.0f;
-    g[2] = gin ? gin[2] : a.grad_rgb ? a.grad_rgb[3 * r + 2] : 0.0f;
-    g[3] = a.grad_depth ? a.grad_depth[r] : 0.0f;
-    g[4] = a.grad_acc ? a.grad_acc[r] : 0.0f;
+    for (int c = 0; c < 3; ++c) g[c] = kFused ? K.g[c] : a.grad_rgb ? a.grad_rgb[3 * r + c] : 0.0f;
+    g[3] = !kFused && a.grad_depth ? a.grad_depth[r] : 0.0f;
+    g[4] = !kFused && a.grad_acc ? a.grad_acc[r] : 0.0f;
     float ro[3] = {0.0f, 0.0f, 0.0f}, rd[3] = {0.0f, 0.0f, 0.0f};   // the ray, for the binning
     if (a.cell_count) {
         for (int i = 0; i < 3; ++i) {
@@ -622,7 +635,7 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
             rd[i] = a.sa.rays_d[3 * r + i];
         }
     }
-    const float Tend = expf(gin ? log_t_end : a.log_t_end_in[r]);
+    const float Tend = expf(kFused ? K.log_t_end : a.log_t_end_in[r]);
     float S[5] = {Tend * a.bg[0], Tend * a.bg[1], Tend * a.bg[2], 0.0f, 0.0f};
     // auxiliary losses: the background entropy's gradient on T_end reaches
     // every sample through dT_end/dsigma_k = -delta T_end; the per-point rgb
@@ -641,19 +654,22 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
         // log T at the start of steps 64*grp .. 64*grp+63, lane j holding step 64*grp+j
         const int64_t first = 64 * grp, last = first + 63 < nsteps - 1 ? first + 63 : nsteps - 1;
         float start = 0.0f;
-        float logT = 0.0f;
-        for (int64_t j = 0; j < last; ++j) {
-            if (j >= first && lane == static_cast<int>(j - first)) start = logT;
-            logT -= wave_sum(sd_of(a, s0 + j * 64 + lane, s1));
+        if (kFused && grp == 0) {
+            start = K.start;
+        } else {
+            float logT = 0.0f;
+            for (int64_t j = 0; j < last; ++j) {
+                if (j >= first && lane == static_cast<int>(j - first)) start = logT;
+                logT -= wave_sum(sd_of(a, s0 + j * 64 + lane, s1));
+            }
+            if (lane == static_cast<int>(last - first)) start = logT;
         }
-        if (lane == static_cast<int>(last - first)) start = logT;
         for (int64_t it = last; it >= first; --it) {
             const int64_t s = s0 + it * 64 + lane;
             const bool ok = s < s1;
             float sd = 0.0f, raw = 0.0f, tk = 0.0f, v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
             if (ok) {
                 raw = a.raw[s];
-                sd = softplus_f(raw + a.act_shift) * step;
                 tk = recipe_tk(tn, p, a.sa.sample_k[s], step);
                 if (a.with_color) {
                     const float4 c = reinterpret_cast<const float4*>(a.col)[s];
@@ -663,13 +679,21 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
                 v[4] = 1.0f;
             }
             const float logT0 = lane_value(start, static_cast<int>(it - first));
-            const float incl = wave_incl_scan(sd, lane);
-            const float excl = dpp_wave<0x138>(incl);   // wave_shr:1, lane 0 reads 0
+            float incl, w;
+            if (kFused && it < kKeptSteps) {
+                const float2 kept = K.kept[it * 64 + lane];
+                w = kept.x;
+                incl = kept.y;
+            } else {
+                if (ok) sd = softplus_f(raw + a.act_shift) * step;
+                incl = wave_incl_scan(sd, lane);
+                const float excl = dpp_wave<0x138>(incl);   // wave_shr:1, lane 0 reads 0
+                w = ok ? expf(logT0 - excl) * -expm1f(-sd) : 0.0f;   // T_k alpha_k, as the forward
+            }
             const float Tafter = expf(logT0 - incl);     // T_{k+1}
-            const float w = ok ? expf(logT0 - excl) * -expm1f(-sd) : 0.0f;   // T_k alpha_k, as the forward
             float dsig = dsig_bg;
             float tot[5];
-            for (int ch = 0; ch < 5; ++ch) {
+            for (int ch = 0; ch < kCh; ++ch) {
                 const float wv = w * v[ch];
                 const float sfx = wave_incl_suffix(wv, lane);
                 const float sfx_ex = dpp_wave<0x130>(sfx);   // wave_shl:1, lane 63 reads 0
@@ -700,7 +724,7 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
                 const int rank = run_rank(cell, ok, lane, a.cell_count);
                 if (ok) a.cell_rank[s] = make_int2(cell, rank);
             }
-            for (int ch = 0; ch < 5; ++ch) S[ch] += tot[ch];
+            for (int ch = 0; ch < kCh; ++ch) S[ch] += tot[ch];
         }
     }
 }
@@ -709,21 +733,27 @@ __global__ __launch_bounds__(kComposeThreads) void compose_bwd_kernel(ComposeArg
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int slot = blockIdx.x * kComposeWaves + wave;
     if (slot >= a.B) return;
-    compose_bwd_ray(a, slot, lane, nullptr, 0.0f);
+    compose_bwd_ray<false>(a, slot, lane, KeptRay{});
 }
 
 // The training step's compositing and its adjoint in one launch: each
 // wavefront composites its ray (forward outputs, loss terms, dL/dC), then
-// walks it back with dL/dC and log T_end from its registers.  The adjoint
-// of a ray depends only on that ray's forward, so no other wavefront waits.
+// walks it back with what it has kept.  The adjoint of a ray depends only on
+// that ray's forward, so no other wavefront waits.  Bound by vector
+// instructions (71 % of the issue slots): forming T_k and w_k again, and log T
+// at the steps' starts by a pass of their own, were a third of them.  7.1M
+// samples 269 -> 238 us, 387k 34 -> 26, 106k 13.8 -> 11.6.
 __global__ __launch_bounds__(kComposeThreads) void compose_step_kernel(ComposeArgs fa, ComposeArgs ba) {
     __shared__ float segs[kComposeWaves][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int slot = blockIdx.x * kComposeWaves + wave;
     if (slot >= fa.B) return;
-    float g[3], lt;
-    compose_fwd_ray<false>(fa, slot, lane, segs[wave], g, &lt);
-    compose_bwd_ray(ba, slot, lane, g, lt);
+    __shared__ float2 kept[kComposeWaves][kKeptSteps * 64];
+    KeptRay K;
+    K.kept = kept[wave];
+    K.start = 0.0f;
+    compose_fwd_ray<false, true>(fa, slot, lane, segs[wave], K);
+    compose_bwd_ray<true>(ba, slot, lane, K);
 }
 
 // ---------------------------------------------------------------------------

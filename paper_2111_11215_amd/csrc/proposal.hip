@@ -232,13 +232,17 @@ __device__ __forceinline__ float exp_recipe(float x) {
 // float32 recipe, no contraction: m = max(0, z), e = exp_recipe(z - m); the
 // total (transmitted entry last), the probabilities e/tot and the mass are
 // summed one term at a time in index order over both halves, so both lanes
-// hold the identical sums; the selection takes the largest unchosen q each
-// round (ties to the lower index), comparing the two halves' candidates, and
-// adds it to the running sum until that reaches cum_frac * mass.
+// hold the identical sums; the selection takes the segments by descending q
+// (ties to the lower index) and adds them one at a time until the sum reaches
+// cum_frac * mass.  The order comes from counting, 32 comparisons per segment
+// (taking the largest of the rest in up to 32 rounds was a chain of compares
+// and lane exchanges: the kernel 24.6 -> 16.7 us for 8192 rays).
 __device__ __forceinline__ int seg_rr(int s) { return 4 * (s >> 3) + (s & 3); }   // inverse of acc_row
 __device__ __forceinline__ int seg_h(int s) { return (s >> 2) & 1; }
 
-__device__ uint32_t select_mask_pair(const float z[16], int h, float cum_frac, float min_mass, float* pred_mass) {
+// sorted: 32 floats of the ray in LDS.
+__device__ uint32_t select_mask_pair(const float z[16], int h, float cum_frac, float min_mass, float* sorted,
+                                     float* pred_mass) {
 #pragma clang fp contract(off)
     float mx = 0.0f;
     #pragma unroll
@@ -262,31 +266,43 @@ __device__ uint32_t select_mask_pair(const float z[16], int h, float cum_frac, f
     #pragma unroll
     for (int s = 0; s < kS; ++s) mass += seg_h(s) == h ? q[seg_rr(s)] : pq[seg_rr(s)];
     *pred_mass = mass;
-    if (!(mass >= min_mass)) return 0xFFFFFFFFu;
-    const float target = cum_frac * mass;
-    uint32_t own = 0, mask = 0;   // own: chosen bits over rr
-    float acc = 0.0f;
-    for (int it = 0; it < kS; ++it) {
-        float bq = -1.0f;
-        int bs = 64, brr = -1;
+    // the number of segments chosen before each of the lane's own: those with
+    // a larger q, or an equal one and a lower index
+    int rank[16];
+    #pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        int n = 0;
         #pragma unroll
-        for (int rr = 0; rr < 16; ++rr)
-            if (!((own >> rr) & 1u) && q[rr] > bq) {
-                bq = q[rr];
-                bs = acc_row(rr, h);
-                brr = rr;
-            }
-        const float oq = __shfl_xor(bq, 32, 64);
-        const int os = __shfl_xor(bs, 32, 64);
-        const bool theirs = oq > bq || (oq == bq && os < bs);
-        const float wq = theirs ? oq : bq;
-        const int ws = theirs ? os : bs;
-        if (!theirs && brr >= 0) own |= 1u << brr;
-        if (ws < kS) mask |= 1u << ws;
-        acc += wq;
-        if (acc >= target) break;
+        for (int k = 0; k < 16; ++k) {
+            if (k < i) n += q[k] >= q[i];
+            if (k > i) n += q[k] > q[i];
+            // segment 8 (k/4) + 4 (1 - h) + k%4 of the other lane
+            if (k / 4 < i / 4) n += pq[k] >= q[i];
+            if (k / 4 > i / 4) n += pq[k] > q[i];
+            if (k / 4 == i / 4) n += h ? pq[k] >= q[i] : pq[k] > q[i];
+        }
+        rank[i] = n;
     }
-    return mask;
+    #pragma unroll
+    for (int rr = 0; rr < 16; ++rr) sorted[rank[rr]] = q[rr];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const float target = cum_frac * mass;
+    float acc = 0.0f;
+    int chosen = 0;
+    bool reached = false;
+    #pragma unroll
+    for (int it = 0; it < kS; ++it) {
+        chosen += reached ? 0 : 1;
+        acc += sorted[it];
+        reached = reached || acc >= target;
+    }
+    uint32_t mask = 0;
+    #pragma unroll
+    for (int rr = 0; rr < 16; ++rr) mask |= rank[rr] < chosen ? 1u << acc_row(rr, h) : 0u;
+    mask |= __shfl_xor(mask, 32, 64);
+    return mass >= min_mass ? mask : 0xFFFFFFFFu;
 }
 
 constexpr int kRaysPerWave = 32;
@@ -314,8 +330,9 @@ __global__ __launch_bounds__(64) void proposal_fwd_kernel(PropArgs a, int run_ne
         #pragma unroll
         for (int rr = 0; rr < 16; ++rr) z[rr] = ray_ok ? logits[static_cast<int64_t>(r) * kS + acc_row(rr, h)] : 0.0f;
     }
+    __shared__ float sorted[kWaves * kRaysPerWave][kS + 1];
     float pm;
-    uint32_t mask = select_mask_pair(z, h, cum_frac, min_mass, &pm);
+    uint32_t mask = select_mask_pair(z, h, cum_frac, min_mass, sorted[wave * kRaysPerWave + m], &pm);
     if (ray_ok && h == 0) {
         if (!meets) mask = 0xFFFFFFFFu;
         if (pred_mass) pred_mass[r] = pm;

@@ -266,6 +266,9 @@ __device__ uint32_t select_mask_pair(const float z[16], int h, float cum_frac, f
     #pragma unroll
     for (int s = 0; s < kS; ++s) mass += seg_h(s) == h ? q[seg_rr(s)] : pq[seg_rr(s)];
     *pred_mass = mass;
+    // (early in training most rays fall back: 335 steps from the start 15.9 ->
+    // 12.0 us per call with this test, 13.0 with the rounds)
+    if (!__any(mass >= min_mass)) return 0xFFFFFFFFu;
     // the number of segments chosen before each of the lane's own: those with
     // a larger q, or an equal one and a lower index
     int rank[16];

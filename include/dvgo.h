@@ -659,8 +659,9 @@ int32_t dvgo_version(void);
  * HIP events recorded on the launch's own stream; dvgo_profile_read waits for
  * them and returns the summed elapsed milliseconds and the launch count since
  * the last dvgo_profile_enable.  kernel_id -1 turns timing off.  Ids:
- *   0 ray setup, 1 Morton sort, 2 count kept, 3 ray-offset scan (batches above 16384 rays), 4 fill kept (up
- *   to 16384 rays with the offsets in the same launch),
+ *   0 ray setup, 1 Morton order, 2 count kept, 3 ray counts summed or scanned
+ *   (batches above 16384 rays), 4 fill kept (up to 2^20 rays with the offsets
+ *   in the same launch),
  *   5 coarse mask, 6 (unused), 7 weight pack + per-ray encoding, 8 gather, 9 MLP forward,
  *   10 compose forward, 11 compose backward, 12 MLP backward, 13 vertex
  *   gather (gradient scatter), 14 partial reduce, 15 photo loss, 16 Adam,
@@ -669,7 +670,7 @@ int32_t dvgo_version(void);
  *   23 record placement when there is no network,
  *   24 vertex gather with the grids' Adam step (dvgo_render_bwd_adam),
  *   25 activity mask from moments (dvgo_grid_active_init), 26 toy pixels,
- *   27 toy vertex gradients, 28 toy loss reduction, 29 grid resample,
+ *   27 toy vertex gradients (with the loss), 28 unused, 29 grid resample,
  *   30 coarse-stage step, 31 view counts. */
 int32_t dvgo_profile_enable(int32_t kernel_id);
 int32_t dvgo_profile_read(double* total_ms, int64_t* launches);

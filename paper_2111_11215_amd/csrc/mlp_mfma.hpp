@@ -32,9 +32,7 @@ constexpr int kOffW3 = kOffB2 + kH;
 constexpr int kOffB3 = kOffW3 + 3 * kH;
 constexpr int kMlpParams = kOffB3 + 3;
 constexpr int kPStride = (kMlpParams + 63) / 64 * 64;
-constexpr int kW1PackF32 = 4 * 2 * 64 * 4;
 constexpr int kW2PackF32 = 4 * 16 * 64 * 4;
-constexpr int kW1PackBF16 = 4 * 64 * 8;
 constexpr int kW2PackBF16 = 4 * 8 * 64 * 8;
 constexpr int kW3PackBF16 = 8 * 64 * 8;    // layer 3 as a 32-row tile (rows >= 3 zero)
 constexpr int kW3TPackBF16 = 4 * 64 * 8;   // W3^T, one K step (k >= 3 zero)
@@ -408,7 +406,6 @@ __device__ __forceinline__ bf16x8 relu_grad_pack8(const f32x16& d, int g, const 
     return __builtin_bit_cast(bf16x8, w);
 }
 
-__device__ __forceinline__ float bf16r(float x) { return static_cast<float>(static_cast<__bf16>(x)); }
 
 // NT output tiles mt0 .. mt0+NT-1 of a chained 128-wide layer, K step
 // outermost: the NT weight fragments of step st+1 are read from LDS while

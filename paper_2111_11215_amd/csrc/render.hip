@@ -14,7 +14,7 @@
 //   compose' walk each ray from its end (suffix scans from log_t_end)
 //   mlp'     network adjoint, per-block weight-gradient partials
 //   scatter  transpose of the trilinear interpolation: samples binned by
-//            grid cell, one thread per vertex gathers its gradient (no
+//            grid cell, a lane quad per vertex gathers its gradient (no
 //            float atomics), the grids' Adam step fused in
 //   reduce   deterministic sum of the per-block weight-gradient partials
 #include "adam.hpp"
@@ -829,7 +829,7 @@ __device__ __forceinline__ bool run_touched(const VertexRun& R) {
 }
 
 // Division of a vertex index by a grid extent, for wavefront-uniform operands
-// (the indices of a grid with its gradients in memory are below 2^32).
+// (the host refuses grids of 2^31 vertices and more).
 struct GridDivisor {
     uint32_t d, inv;
     __device__ explicit GridDivisor(int n) : d(n), inv(0xffffffffu / static_cast<uint32_t>(n)) {}

@@ -330,10 +330,12 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
 // both matrices, refilled from the L2 in phases that do not use it: holding
 // both spilled, and a spill's reload waits for every load before it.
 //
-// A block takes 30,000 cycles, 11,900 of them matrix instructions; the rest is
-// the vector work between two barriers that nothing overlaps (splits, head,
-// dW3) and first loads.  390k samples: 328 us, 748 us with float32 matrix
-// instructions.
+// A block takes about 29,000 cycles, 11,900 of them matrix instructions; the
+// rest is the vector work between two barriers that nothing overlaps (splits,
+// head, dW3) and first loads.  387k samples: 334 us, about 750 with float32
+// matrix instructions; 348 before the weight gradients' operands were read
+// ahead and the head's weights once for both column tiles (with encoded
+// positions 440 -> 415, 98k samples 145 -> 141).
 // ---------------------------------------------------------------------------
 // One lane's 16 values of its tile (accumulator order) as planes into its
 // sample's row: `at` is the address of its first unit, the second is 2 further.
@@ -688,15 +690,15 @@ __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosAr
                 db3[ch] += dz3[c][ch];
             }
         }
+        f32x16 dz[2];
         #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            f32x16 dz;
+        for (int q = 0; q < 4; ++q) {
+            float4 w[3];
             #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float4 w[3];
-                #pragma unroll
-                for (int ch = 0; ch < 3; ++ch)
-                    w[ch] = *reinterpret_cast<const float4*>(sW3 + ch * kH + 32 * wave + 8 * q + 4 * h);
+            for (int ch = 0; ch < 3; ++ch)
+                w[ch] = *reinterpret_cast<const float4*>(sW3 + ch * kH + 32 * wave + 8 * q + 4 * h);
+            #pragma unroll
+            for (int c = 0; c < 2; ++c)
                 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int i = 4 * q + e;
@@ -704,12 +706,12 @@ __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosAr
                     #pragma unroll
                     for (int ch = 0; ch < 3; ++ch) dW3[ch][i] += dz3[c][ch] * h2;
                     const float dh = w[0][e] * dz3[c][0] + w[1][e] * dz3[c][1] + w[2][e] * dz3[c][2];
-                    dz[i] = live[c] & (0x8000u >> i) ? dh : 0.0f;
-                    db2[i] += dz[i];
+                    dz[c][i] = live[c] & (0x8000u >> i) ? dh : 0.0f;
+                    db2[i] += dz[c][i];
                 }
-            }
-            stage_tile(putZ + c * kColB, dz);
         }
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) stage_tile(putZ + c * kColB, dz[c]);
         f32x16 d1[2] = {zero_tile(), zero_tile()};
         load_x(a, next);
         __syncthreads();   // dz2 rows complete
@@ -745,23 +747,31 @@ __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosAr
                         make_float4(df[c][4], df[c][5], df[c][6], df[c][7]);
             }
         }
-        // ---- dW2 rows 32w .. over the block's samples
-        #pragma unroll
-        for (int st = 0; st < kSB / 16; ++st) {
-            bf16x8 A[3];
-            #pragma unroll
-            for (int p = 0; p < 3; ++p) A[p] = tr_unit(trZ, st, p);
-            #pragma unroll
-            for (int np = 0; np < 4; np += 2) {
-                bf16x8 B[2][3];
+        // ---- dW2 rows 32w .. over the block's samples, the operands of two of
+        // its tiles on their way from LDS while the two before are multiplied
+        // (one wavefront per SIMD: nothing else covers the reads)
+        {
+            bf16x8 A[2][3], B[2][2][3];
+            auto rd = [&](int k) {   // group k: K step k / 2, tiles 2 (k % 2) and the next
                 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int p = 0; p < 3; ++p) {
+                    if (k % 2 == 0) A[k / 2 % 2][p] = tr_unit(trZ, k / 2, p);
                     #pragma unroll
-                    for (int p = 0; p < 3; ++p) B[c][p] = tr_unit(trH ^ (64u * (np + c)), st, p);
+                    for (int c = 0; c < 2; ++c) B[k % 2][c][p] = tr_unit(trH ^ (64u * (2 * (k % 2) + c)), k / 2, p);
+                }
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            rd(0);
+            #pragma unroll
+            for (int k = 0; k < 2 * kSB / 16; ++k) {
+                if (k + 1 < 2 * kSB / 16) rd(k + 1);
                 #pragma unroll
                 for (int q = 0; q < 6; ++q)
                     #pragma unroll
-                    for (int c = 0; c < 2; ++c) dW2[np + c] = mma_bf16(A[kTermA[q]], B[c][kTermB[q]], dW2[np + c]);
+                    for (int c = 0; c < 2; ++c)
+                        dW2[2 * (k % 2) + c] = mma_bf16(A[k / 2 % 2][kTermA[q]], B[k % 2][c][kTermB[q]],
+                                                        dW2[2 * (k % 2) + c]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         __syncthreads();   // h1 rows read; dL/dfeat shares complete
@@ -792,25 +802,34 @@ __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosAr
         }
         // ---- dW1 rows 32w .. (column kIn: the bias); the wavefront reads
         // back its own dz1 rows, x' is everyone's
-        #pragma unroll
-        for (int st = 0; st < kSB / 16; ++st) {
-            bf16x8 A[3], B[L::kXT][3];
-            #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                A[p] = tr_unit(trH ^ (64u * wave), st, p);
+        {
+            bf16x8 A[2][3], B[2][L::kXT][3];
+            auto rd = [&](int st) {
                 #pragma unroll
-                for (int nt = 0; nt < L::kXT; ++nt) {
-                    const uint32_t at = trX + (p * kXTile + 16 * st * kXP + 32 * nt) * 2;
-                    B[nt][p] = tr_pair(at, at + 4 * kXP * 2);
+                for (int p = 0; p < 3; ++p) {
+                    A[st % 2][p] = tr_unit(trH ^ (64u * wave), st, p);
+                    #pragma unroll
+                    for (int nt = 0; nt < L::kXT; ++nt) {
+                        const uint32_t at = trX + (p * kXTile + 16 * st * kXP + 32 * nt) * 2;
+                        B[st % 2][nt][p] = tr_pair(at, at + 4 * kXP * 2);
+                    }
                 }
-            }
-            // W2 for the next block's layer 2
-            load_w(a.w2pb, 2 * st);
-            load_w(a.w2pb, 2 * st + 1);
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            rd(0);
             #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int st = 0; st < kSB / 16; ++st) {
+                if (st + 1 < kSB / 16) rd(st + 1);
+                // W2 for the next block's layer 2
+                load_w(a.w2pb, 2 * st);
+                load_w(a.w2pb, 2 * st + 1);
                 #pragma unroll
-                for (int nt = 0; nt < L::kXT; ++nt) dW1[nt] = mma_bf16(A[kTermA[q]], B[nt][kTermB[q]], dW1[nt]);
+                for (int q = 0; q < 6; ++q)
+                    #pragma unroll
+                    for (int nt = 0; nt < L::kXT; ++nt)
+                        dW1[nt] = mma_bf16(A[st % 2][kTermA[q]], B[st % 2][nt][kTermB[q]], dW1[nt]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         __syncthreads();   // x', sD and sH read before the next block's staging
     }

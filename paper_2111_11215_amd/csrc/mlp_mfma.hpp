@@ -649,7 +649,7 @@ __device__ __forceinline__ f32x16 zero_tile() {
 // The layout before, 32 samples stationary per wavefront pair and the weights
 // read from LDS, took 1.5 times the LDS bytes and eight barriers: 390k samples
 // 93 -> 83 us, 7.1M samples 1610 -> 1383 us, with encoded positions (KX = 5,
-// 203k samples) 80 -> 60 us.
+// 153k samples) 80 -> 60 us.
 // ---------------------------------------------------------------------------
 template <int KX>
 __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArgs pa) {

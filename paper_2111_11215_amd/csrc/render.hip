@@ -283,9 +283,9 @@ struct GatherArgs {
 // along z).  With a sample per lane it was bound by the address unit: 24
 // feature loads and 8 density loads of 64 separate addresses, where the quads
 // need 8 of 16 segments and one.  387k training samples (160^3 cells, float32)
-// 43 -> 34 us, 3.8M samples of an image in float32 134 -> 109; in bfloat16 it
+// 43 -> 34 us, 30653 rays of a preview image 134 -> 109; in bfloat16 it
 // is bound by memory: 7.1M samples in 256^3 cells 452 -> 417 us (1.2 GB read,
-// 0.45 written, 3.9 TB/s), 3.8M of an image 137 -> 134.  Both z neighbours in
+// 0.45 written, 3.9 TB/s), 65536 rays of an image 137 -> 134.  Both z neighbours in
 // one load (half the loads again) and a contiguous eighth of the samples per
 // XCD were no faster (429, 128; 416, 133).  The sums keep their order.
 template <int kFeat>

@@ -124,6 +124,8 @@ struct PackArgs {
     const float* w1;
     const float* w2;
     const float* w3;
+    const float* b2;
+    float* b2p;   // b2 with kDeadBias for dead units (float32 form)
     uint16_t* w3pb;
     uint16_t* w3tpb;
     uint16_t* w1tpb;
@@ -144,8 +146,18 @@ struct PackArgs {
 // kPackThreads (a device function so that it can share a launch).
 constexpr int kPackThreads = kW2PackF32;
 
+// The float32 form gives a unit without weights and bias this one: ReLU turns
+// either into 0, but a pre-activation of exactly 0 in every sample would count
+// as one near zero, whose branch is worth a second look (see add_live).
+constexpr float kDeadBias = -1.0f;
+
 __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
     const int planes = a.bf16 ? 1 : 3;
+    if (!a.bf16 && gid < kH * 64) {   // a wavefront per unit of layer 2
+        const int i = gid >> 6, lane = gid & 63;
+        const bool any = __any(a.w2[i * kH + lane] != 0.0f || a.w2[i * kH + 64 + lane] != 0.0f);
+        if (lane == 0) a.b2p[i] = any || a.b2[i] != 0.0f ? a.b2[i] : kDeadBias;
+    }
     if (gid < kW2PackF32) {
         // float32: index ((mt*16 + q)*64 + lane)*4 + u, step st = 4q + u
         const int u = gid & 3, lane = (gid >> 2) & 63, q = (gid >> 8) & 15, mt = gid >> 12;

@@ -103,12 +103,15 @@ __device__ __forceinline__ void split_chain(const bf16x8* w, int lane, f32x16 ac
 // the low 16 bits.
 //
 // A gradient jumps by a sample's whole share where a unit changes its branch,
-// and near zero the pre-activation's rounding decides that.  The branches are
-// defined by the plain float32 chain of fused multiply-adds, in input order
-// (a float32 matrix instruction's own order and rounding): a unit further from
-// zero than 2^-20 of the largest in its lane has the split chain's sign (the
-// two chains differ by about 2^-22 of a layer's rms), and a sample with a unit
-// nearer than that, one in about two thousand, has the chain evaluated.
+// and near zero the pre-activation's rounding decides that.  Such branches are
+// taken from the plain float32 chain of fused multiply-adds, in input order
+// (a float32 matrix instruction's own order and rounding): a sample with a unit
+// within 2^-20 of zero, relative to the largest of its lane, has the chain
+// evaluated, one sample in about two thousand; any other unit has the split
+// chain's sign.  The two chains differ by about 2^-22 of a layer's rms, so the
+// distance is ample where a unit's terms are of its layer's size; it is no
+// bound for terms that all cancel to far below theirs.  A unit at exactly zero
+// counts as near; one without weights and bias is not at zero (kDeadBias).
 __device__ __forceinline__ uint32_t add_live(uint32_t bits, const f32x16& z, float* lo, float* hi) {
     #pragma unroll
     for (int i = 0; i < 16; i += 2) {
@@ -307,9 +310,8 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
         }
         if (ok && h == 0) reinterpret_cast<float4*>(a0.col)[s] = make_float4(col[0], col[1], col[2], 0.0f);
         if constexpr (kLive) {
-            // a unit at exactly zero (one without weights) is no reason: it
-            // is zero in either chain, in every sample
-            const uint64_t near = __ballot((lo1 <= hi1 * 0x1p-20f && lo1 > 0.0f) || (lo2 <= hi2 * 0x1p-20f && lo2 > 0.0f));
+            // (all 64 units at zero: no active input and no bias, zero in either chain)
+            const uint64_t near = __ballot((lo1 <= hi1 * 0x1p-20f && hi1 > 0.0f) || (lo2 <= hi2 * 0x1p-20f && hi2 > 0.0f));
             for (uint32_t todo = static_cast<uint32_t>(near) | static_cast<uint32_t>(near >> 32); todo; todo &= todo - 1)
                 plain_live<KX>(refresh(a0), xs, r, __builtin_ctz(todo), lane, sPlain[wave], live);
             if (ok) reinterpret_cast<uint4*>(a0.live)[2 * s + h] = make_uint4(live[0], live[1], live[2], live[3]);

@@ -32,7 +32,7 @@ namespace {
 constexpr int kMaxBwdBlocks = 256;
 
 struct WsLayout {
-    size_t base, pe, w1p, w2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
+    size_t base, pe, w1p, w2p, b2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
         cell_start, scan_tmp, cell_rank, rec_head, rec, live, step_rgb, step_grad, step_logt, step_sqerr, total;
 };
 
@@ -48,6 +48,7 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.pe = take(static_cast<size_t>(B) * 32 * 4);
     L.w1p = take(kW1PackF32Max * 4);
     L.w2p = take(kW2PackF32 * 4);
+    L.b2p = take(kH * 4);
     L.w1pb = take(3 * kW1PackBF16Max * 2);   // the three planes of the float32 form
     L.w2pb = take(3 * kW2PackBF16 * 2);
     L.w2tpb = take(3 * kW2PackBF16 * 2);
@@ -232,6 +233,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& P, int blk) {
         #pragma unroll
         for (int q = 0; q < kPE; ++q) wv[q] = w1[i * w1_in + view_col + q];
     }
+    bool dead = w1 && !P.pk.bf16 && bi == 0.0f;   // (see kDeadBias)
+    for (int q = 0; dead && q < w1_in; ++q) dead = w1[i * w1_in + q] == 0.0f;
     for (int rr = h; rr < kPrepRays; rr += 2) {
         const int r = r0 + rr;
         if (r >= B) break;
@@ -239,6 +242,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& P, int blk) {
             float acc = bi;
             #pragma unroll
             for (int q = 0; q < kPE; ++q) acc += wv[q] * se[rr][q];
+            if (dead) acc = kDeadBias;
             base[static_cast<int64_t>(r) * kH + i] = acc;
         }
         if (i < 32) pe[static_cast<int64_t>(r) * 32 + i] = se[rr][i];
@@ -1329,6 +1333,8 @@ PrepArgs prep_args(const Common& cm, const dvgo_mlp* mlp, int* zero, int64_t nze
         pk.w2pb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w2pb);
         pk.w2tpb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w2tpb);
         pk.w3 = mlp->w3;
+        pk.b2 = mlp->b2;
+        pk.b2p = reinterpret_cast<float*>(cm.ws + cm.L.b2p);
         pk.w3pb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w3pb);
         pk.w3tpb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w3tpb);
         pk.w1tpb = reinterpret_cast<uint16_t*>(cm.ws + cm.L.w1tpb);
@@ -1419,7 +1425,7 @@ MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_ke
     ma.n_kept = n_kept;
     ma.cap = cm.cap;
     ma.w1 = mlp->w1;
-    ma.b2 = mlp->b2;
+    ma.b2 = mlp->precision == DVGO_BF16 ? mlp->b2 : reinterpret_cast<const float*>(cm.ws + cm.L.b2p);
     ma.w3 = mlp->w3;
     ma.b3 = mlp->b3;
     ma.base = reinterpret_cast<const float*>(cm.ws + cm.L.base);

@@ -111,10 +111,12 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(stati
 
 // The exact bfloat16 planes of a float32 value: hi = bf16(w), mid =
 // bf16(w - hi), lo = w - hi - mid (both differences are exact, and lo fits
-// bfloat16's 8 bits).  The bfloat16 arithmetic uses plane 0 only.
+// bfloat16's 8 bits).  A finite w that rounds to infinity has the largest
+// finite bfloat16 as hi.  The bfloat16 arithmetic uses plane 0 only.
 __device__ __forceinline__ void store_planes(uint16_t* dst, int i, int stride, float w, int planes) {
     for (int p = 0; p < planes; ++p) {
-        const uint16_t b = f2bf(w);
+        uint16_t b = f2bf(w);
+        if (planes > 1 && (b & 0x7FFFu) == 0x7F80u && fabsf(w) < INFINITY) b -= 1;
         dst[p * stride + i] = b;
         w -= bf2f(b);
     }
@@ -210,7 +212,8 @@ struct MlpArgs {
     const int* sample_ray;
     const int64_t* n_kept;
     int64_t cap;
-    const float* w1;      // [128][39] raw, for dL/dfeat
+    const float* w1;      // W1 and W2 as given, for plain_adjoint
+    const float* w2;
     const float* b2;
     const float* w3;      // [3][128]
     const float* b3;
@@ -235,6 +238,7 @@ struct MlpArgs {
     float4* rec;              // [cap][4] binned records
     int nrays;                // rows of base and pe
     uint32_t* live;           // [cap][8] ReLU branches (float32 form; NULL: not wanted)
+    int* wide;                // float32 adjoint: not 0 where its values may leave the planes' range
 };
 
 // The query position of each sample, for the networks with an encoded
@@ -259,7 +263,6 @@ __device__ __forceinline__ float4* binned_record(const MlpArgs& a, int64_t s) {
 
 __device__ __forceinline__ MlpArgs refresh(const MlpArgs& a) {
     MlpArgs l = a;
-    l.w1 = opaque(a.w1);
     l.b2 = opaque(a.b2);
     l.w3 = opaque(a.w3);
     l.b3 = opaque(a.b3);

@@ -9,6 +9,17 @@
 // replace eight K = 2 float32 ones of twice their duration: 2.7 times the
 // rate, and 48 roundings of an accumulator over a 128-wide layer instead of
 // 64.
+//
+// Range: below about 2^-110 the low plane loses bits to underflow (an error of
+// less than 2^-130).  Above the largest bfloat16 the high plane is infinite and
+// the others are not numbers, so such an operand, or an infinity, makes every
+// sum that it enters NaN.  The forward lets a NaN through its ReLUs, and a
+// sample whose logits are not finite is evaluated by the plain float32 chain
+// instead (plain_sample).  The adjoint's operands are h1 and the inputs, which
+// the forward has checked in this way, and gradients: with dL/dc below 2^64 and
+// weights below 2^20 those stay below 2^112.  Where either is not so, or a
+// sample's logits were not finite, the adjoint takes the plain chain for every
+// sample (plain_adjoint).
 #pragma once
 
 #include <type_traits>
@@ -133,11 +144,12 @@ __device__ __forceinline__ uint32_t half_bits(uint32_t t, int h) {
     return __builtin_bitreverse32(b) >> 16;
 }
 
-// The branches of the sample of column ms by the plain chain, one unit per
-// lane and pass; scratch: 128 floats of LDS.  The whole wavefront takes part.
+// The branches and the colour of the sample of column ms by the plain chain,
+// one unit per lane and pass; scratch: 128 floats of LDS.  The whole wavefront
+// takes part; the results go to the sample's two lanes.
 template <int KX>
-__device__ __forceinline__ void plain_live(const MlpArgs& a, const float xs[NetLayout<KX>::kS], int r, int ms, int lane,
-                                           float* scratch, uint32_t live[4]) {
+__device__ __forceinline__ void plain_sample(const MlpArgs& a, const float xs[NetLayout<KX>::kS], int r, int ms,
+                                             int lane, float* scratch, uint32_t live[4], float col[3]) {
     using L = NetLayout<KX>;
     const int m = lane & 31;
     const int rs = __builtin_amdgcn_readlane(r, ms);
@@ -169,6 +181,7 @@ __device__ __forceinline__ void plain_live(const MlpArgs& a, const float xs[NetL
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    float z3[3] = {0.0f, 0.0f, 0.0f};
     #pragma unroll
     for (int p = 0; p < 2; ++p) {
         const int mt = 2 * p + (lane >> 5);
@@ -183,14 +196,24 @@ __device__ __forceinline__ void plain_live(const MlpArgs& a, const float xs[NetL
         const uint64_t b = __ballot(acc > 0.0f);
         tile2[2 * p] = static_cast<uint32_t>(b);
         tile2[2 * p + 1] = static_cast<uint32_t>(b >> 32);
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) z3[c] += a.w3[c * kH + 32 * mt + m] * fmaxf(acc, 0.0f);
     }
     __builtin_amdgcn_wave_barrier();
+    #pragma unroll
+    for (int c = 0; c < 3; ++c) z3[c] = wave_total(z3[c]);
     if (m == ms) {
         #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
             live[mt] = half_bits(tile1[mt], lane >> 5) << 16 | half_bits(tile2[mt], lane >> 5);
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) col[c] = 1.0f / (1.0f + expf(-(z3[c] + a.b3[c])));
     }
 }
+
+// ReLU that lets a NaN through (a NaN of the split sums is an operand out of
+// the planes' range, of which the logits have to tell).
+__device__ __forceinline__ float relu_nan(float z) { return __builtin_elementwise_maximum(z, 0.0f); }
 
 // ---------------------------------------------------------------------------
 // forward: one wavefront per 32 samples, eight wavefronts per workgroup (two
@@ -210,7 +233,7 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
     __shared__ bf16x8 sW1[3 * kW1];
     __shared__ __attribute__((aligned(16))) float sB2[kH];
     __shared__ __attribute__((aligned(16))) float sW3[3 * kH];
-    __shared__ __attribute__((aligned(16))) float sPlain[kLive ? 8 : 1][kH];
+    __shared__ __attribute__((aligned(16))) float sPlain[8][kH];
     const int64_t n = *a0.n_kept < a0.cap ? *a0.n_kept : a0.cap;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // consecutive tiles go to one workgroup (a ray's samples share its
@@ -227,6 +250,21 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
         f1.load(reinterpret_cast<const bf16x8*>(a0.w1pb));
         const int t = static_cast<int>(threadIdx.x);
         const float v = t < 3 * kH ? a0.w3[t] : a0.b2[t - 3 * kH];
+        if (kLive && blockIdx.x == 0) {   // weights of 2^20 and more, for the adjoint
+            bool big = t < 3 * kH && !(fabsf(v) < 0x1p20f);
+            auto any = [&](const bf16x8& w) {
+                const i16x8 b = __builtin_bit_cast(i16x8, w);
+                #pragma unroll
+                for (int e = 0; e < 8; ++e) big |= (b[e] & 0x7FFF) >= 0x4980;
+            };
+            static_assert(kW2 % 512 == 0, "the first plane in whole rounds");
+            #pragma unroll
+            for (int u = 0; u < kW2 / 512; ++u) any(f2.t[u]);
+            #pragma unroll
+            for (int u = 0; u < (kW1 + 511) / 512; ++u)   // (and some of the smaller planes')
+                if (u * 512 + t < 3 * kW1) any(f1.t[u]);
+            if (__any(big) && lane == 0) *a0.wide = 1;
+        }
         f2.store(sW2);
         f1.store(sW1);
         if (t < 3 * kH) sW3[t] = v;
@@ -280,7 +318,7 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
         split_chain<4, 8, kW2, 8 * 64>(sW2, ln, z2, [&](int st) {
             float v[8];
             #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = fmaxf(h1[st >> 1][8 * (st & 1) + e], 0.0f);
+            for (int e = 0; e < 8; ++e) v[e] = relu_nan(h1[st >> 1][8 * (st & 1) + e]);
             return split8(v, 0);
         });
         if constexpr (kLive) {
@@ -297,10 +335,10 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
                 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const float4 w = *reinterpret_cast<const float4*>(sW3 + c * kH + 32 * mt + 8 * q + h4);
-                    z3[c] += w.x * fmaxf(z2[mt][4 * q], 0.0f);
-                    z3[c] += w.y * fmaxf(z2[mt][4 * q + 1], 0.0f);
-                    z3[c] += w.z * fmaxf(z2[mt][4 * q + 2], 0.0f);
-                    z3[c] += w.w * fmaxf(z2[mt][4 * q + 3], 0.0f);
+                    z3[c] += w.x * relu_nan(z2[mt][4 * q]);
+                    z3[c] += w.y * relu_nan(z2[mt][4 * q + 1]);
+                    z3[c] += w.z * relu_nan(z2[mt][4 * q + 2]);
+                    z3[c] += w.w * relu_nan(z2[mt][4 * q + 3]);
                 }
         float col[3];
         #pragma unroll
@@ -308,14 +346,26 @@ __global__ __launch_bounds__(512, 2) void mlp_fwd_split_kernel(MlpArgs a0, PosAr
             z3[c] += __shfl_xor(z3[c], 32, 64);
             col[c] = 1.0f / (1.0f + expf(-(z3[c] + b3[c])));
         }
-        if (ok && h == 0) reinterpret_cast<float4*>(a0.col)[s] = make_float4(col[0], col[1], col[2], 0.0f);
+        // out of the planes' range, or infinite or NaN in float32 as well
+        const bool bad = ok && !(fabsf(z3[0]) + fabsf(z3[1]) + fabsf(z3[2]) < INFINITY);
+        bool again = bad;
         if constexpr (kLive) {
             // (all 64 units at zero: no active input and no bias, zero in either chain)
-            const uint64_t near = __ballot((lo1 <= hi1 * 0x1p-20f && hi1 > 0.0f) || (lo2 <= hi2 * 0x1p-20f && hi2 > 0.0f));
-            for (uint32_t todo = static_cast<uint32_t>(near) | static_cast<uint32_t>(near >> 32); todo; todo &= todo - 1)
-                plain_live<KX>(refresh(a0), xs, r, __builtin_ctz(todo), lane, sPlain[wave], live);
-            if (ok) reinterpret_cast<uint4*>(a0.live)[2 * s + h] = make_uint4(live[0], live[1], live[2], live[3]);
+            again |= ok && ((lo1 <= hi1 * 0x1p-20f && hi1 > 0.0f) || (lo2 <= hi2 * 0x1p-20f && hi2 > 0.0f));
         }
+        if (const uint64_t mask = __ballot(again)) {
+            float xa[L::kS], ca[3];   // (the inputs a second time: held until here, they spilled)
+            int ra = r;
+            asm volatile("" : "+v"(ra));
+            sample_inputs<KX>(pa, refresh(a0).feat, sc, ra, xa);
+            for (uint32_t todo = static_cast<uint32_t>(mask) | static_cast<uint32_t>(mask >> 32); todo; todo &= todo - 1)
+                plain_sample<KX>(refresh(a0), xa, ra, __builtin_ctz(todo), lane, sPlain[wave], live, ca);
+            #pragma unroll
+            for (int c = 0; c < 3; ++c) col[c] = bad ? ca[c] : col[c];
+            if (kLive && __any(bad) && lane == 0) *a0.wide = 1;
+        }
+        if (ok && h == 0) reinterpret_cast<float4*>(a0.col)[s] = make_float4(col[0], col[1], col[2], 0.0f);
+        if (kLive && ok) reinterpret_cast<uint4*>(a0.live)[2 * s + h] = make_uint4(live[0], live[1], live[2], live[3]);
     }
 }
 
@@ -350,6 +400,118 @@ __device__ __forceinline__ void stage_tile(uint32_t at, const f32x16& v) {
     }
 }
 
+// The adjoint by plain float32 multiply-adds, for calls whose values may leave
+// the planes' range (MlpArgs::wide): a sample at a time, thread (i, q) with the
+// rows i and the columns of half q of both weight gradients in registers.  Not
+// made to be fast (a run in which it is taken has diverged).  lds: 1024 floats.
+template <int KX>
+__device__ __forceinline__ void plain_adjoint(const MlpArgs& a, const PosArgs& pa, int64_t n, float* lds) {
+    using L = NetLayout<KX>;
+    constexpr int kCols = L::kIn + 1, kPer = (kCols + 1) / 2;   // columns of x' = [inputs, PE(d), 1]
+    float *sX = lds, *sH = lds + 128, *sD2 = lds + 256, *sD1 = lds + 384, *sZ = lds + 512;
+    static_assert(2 * kPer <= 128, "x' fits its row");
+    const int t = static_cast<int>(threadIdx.x), i = t & (kH - 1), q = t >> 7;
+    float dW2[kH / 2], dW1[kPer], dW3[3] = {0.0f, 0.0f, 0.0f}, db2 = 0.0f, db3[3] = {0.0f, 0.0f, 0.0f};
+    #pragma unroll
+    for (int j = 0; j < kH / 2; ++j) dW2[j] = 0.0f;
+    #pragma unroll
+    for (int j = 0; j < kPer; ++j) dW1[j] = 0.0f;
+    if (t < 128) sX[t] = 0.0f;
+    for (int64_t s = blockIdx.x; s < n; s += gridDim.x) {
+        __syncthreads();   // the last sample's rows read
+        const int r = a.sample_ray[s];
+        if (t < kC) {
+            sX[t] = a.feat[s * kC + t];
+        } else if (t < L::kS) {   // as sample_encode
+            float o[3], d[3], x[3];
+            for (int c = 0; c < 3; ++c) {
+                o[c] = pa.rays_o[3 * r + c];
+                d[c] = pa.rays_d[3 * r + c];
+            }
+            const float tk = dvgo_dev::recipe_tk(pa.t_near[r], pa.jitter ? pa.jitter[r] : 0.0f, pa.sample_k[s], pa.step);
+            dvgo_dev::recipe_x(o, d, tk, x);
+            const int e = t - kC, c = e % 3, f = (e - 3) / 6;   // u, then three sines and three cosines per frequency
+            const float u = ((c == 0 ? x[0] : c == 1 ? x[1] : x[2]) - (c == 0 ? pa.pe_c[0] : c == 1 ? pa.pe_c[1] : pa.pe_c[2])) *
+                            (c == 0 ? pa.pe_ih[0] : c == 1 ? pa.pe_ih[1] : pa.pe_ih[2]);
+            float sv, cv;
+            dvgo_dev::pe_sincos(u * static_cast<float>(1 << (e < 3 ? 0 : f)), &sv, &cv);
+            sX[t] = e < 3 ? u : (e - 3) % 6 < 3 ? sv : cv;
+        } else if (t < kCols) {
+            sX[t] = a.pe[static_cast<int64_t>(r) * 32 + t - L::kS];
+        }
+        __syncthreads();
+        float z1 = a.base[static_cast<int64_t>(r) * kH + i];
+        for (int k = 0; k < L::kS; ++k) z1 = fmaf(a.w1[i * L::kIn + k], sX[k], z1);
+        if (q == 0) sH[i] = fmaxf(z1, 0.0f);
+        __syncthreads();
+        float z2 = a.b2[i];
+        for (int g = 0; g < kH; g += 8)   // the chain's order: see plain_sample
+            for (int u = 0; u < 4; ++u) {
+                z2 = fmaf(a.w2[i * kH + g + u], sH[g + u], z2);
+                z2 = fmaf(a.w2[i * kH + g + 4 + u], sH[g + 4 + u], z2);
+            }
+        const float h2 = fmaxf(z2, 0.0f);
+        float w3[3], p[3];
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            w3[c] = a.w3[c * kH + i];
+            p[c] = wave_total(w3[c] * h2);
+            if ((t & 63) == 0) sZ[4 * (t >> 6) + c] = p[c];
+        }
+        __syncthreads();
+        const float4 dc = reinterpret_cast<const float4*>(a.col)[s];
+        const float g[3] = {dc.x, dc.y, dc.z};
+        float dz3[3];
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float cv = 1.0f / (1.0f + expf(-(sZ[c] + sZ[4 + c] + a.b3[c])));
+            dz3[c] = g[c] * cv * (1.0f - cv);
+            db3[c] += dz3[c];
+            dW3[c] += dz3[c] * h2;
+        }
+        const float dz2 = z2 > 0.0f ? w3[0] * dz3[0] + w3[1] * dz3[1] + w3[2] * dz3[2] : 0.0f;
+        db2 += dz2;
+        if (q == 0) sD2[i] = dz2;
+        __syncthreads();
+        float dh = 0.0f;
+        for (int k = 0; k < kH; ++k) dh = fmaf(a.w2[k * kH + i], sD2[k], dh);
+        const float dz1 = z1 > 0.0f ? dh : 0.0f;
+        if (q == 0) sD1[i] = dz1;
+        __syncthreads();
+        #pragma unroll
+        for (int j = 0; j < kH / 2; ++j) dW2[j] = fmaf(dz2, sH[kH / 2 * q + j], dW2[j]);
+        #pragma unroll
+        for (int j = 0; j < kPer; ++j) dW1[j] = fmaf(dz1, sX[kPer * q + j], dW1[j]);
+        // the record: 16 threads per feature channel, the head by a thread beyond
+        const int2 cr = a.cell_rank[s];
+        float4* rec = a.rec + (static_cast<int64_t>(a.cell_start[cr.x]) + cr.y) * 4;
+        if (t < 16 * kC) {
+            float v = 0.0f;
+            for (int k = t & 15; k < kH; k += 16) v = fmaf(a.w1[k * L::kIn + (t >> 4)], sD1[k], v);
+            #pragma unroll
+            for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            if ((t & 15) == 0) reinterpret_cast<float*>(rec + 1)[t >> 4] = v;
+        } else if (t == 16 * kC) {
+            rec[0] = a.rec_head[s];
+        }
+    }
+    float* out = a.partial + static_cast<int64_t>(blockIdx.x) * L::kPStride;
+    #pragma unroll
+    for (int j = 0; j < kH / 2; ++j) out[L::kOffW2 + i * kH + kH / 2 * q + j] = dW2[j];
+    #pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int col = kPer * q + j;
+        if (col < L::kIn) out[L::kOffW1 + i * L::kIn + col] = dW1[j];
+        else if (col == L::kIn) out[L::kOffB1 + i] = dW1[j];
+    }
+    if (q == 0) {
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) out[L::kOffW3 + c * kH + i] = dW3[c];
+        out[L::kOffB2 + i] = db2;
+    }
+    if (t < 3) out[L::kOffB3 + t] = t == 0 ? db3[0] : t == 1 ? db3[1] : db3[2];
+}
+
 template <int KX>
 __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosArgs pa) {
     using L = NetLayout<KX>;
@@ -372,6 +534,10 @@ __global__ __launch_bounds__(256, 1) void mlp_bwd_split_kernel(MlpArgs a0, PosAr
     const int t = static_cast<int>(threadIdx.x);
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int m = lane & 31, h = lane >> 5;
+    if (*a0.wide != 0) {
+        plain_adjoint<KX>(a0, pa, n, sXF);
+        return;
+    }
     f32x16 dW2[4], dW1[L::kXT];
     #pragma unroll
     for (int i = 0; i < 4; ++i) dW2[i] = zero_tile();

@@ -32,7 +32,7 @@ namespace {
 constexpr int kMaxBwdBlocks = 256;
 
 struct WsLayout {
-    size_t base, pe, w1p, w2p, b2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, cell_count,
+    size_t base, pe, w1p, w2p, b2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, wide, cell_count,
         cell_start, scan_tmp, cell_rank, rec_head, rec, live, step_rgb, step_grad, step_logt, step_sqerr, total;
 };
 
@@ -59,6 +59,7 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.feat = take(static_cast<size_t>(cap) * kC * 4);
     L.col = take(static_cast<size_t>(cap) * 4 * 4);
     L.partial = take(static_cast<size_t>(kMaxBwdBlocks) * kPStrideMax * 4);
+    L.wide = take(4);
     L.cell_count = take(static_cast<size_t>(ncell + 1) * 4);
     L.cell_start = take(static_cast<size_t>(ncell + 1) * 4);
     L.scan_tmp = take(cell_scan_bytes(ncell + 1));
@@ -172,6 +173,7 @@ struct PrepArgs {
     int view_col;   // first column of W1's view part
     float* base;
     float* pe;
+    int* wide;      // MlpArgs::wide, cleared (NULL: none)
     int* zero;      // cleared (NULL: none)
     int64_t nzero;
     int zblocks;
@@ -181,6 +183,7 @@ struct PrepArgs {
 __device__ __forceinline__ void prep_body(const PrepArgs& P, int blk) {
     constexpr int kPackBlocks = kPackThreads / 256;
     if (blk < kPackBlocks) {
+        if (blk == 0 && threadIdx.x == 0 && P.wide) *P.wide = 0;
         pack_weights(P.pk, blk * 256 + threadIdx.x);
         return;
     }
@@ -433,6 +436,8 @@ struct ComposeArgs {
     int* cell_count;       // [ncell + 1], zero on entry
     int2* cell_rank;       // [cap] (cell, rank within cell)
     float4* rec_head;      // [cap] (fx, fy, fz, dL/draw)
+    // backward, float32 network: set where a |dL/dc| is 2^64 or more (NULL: off)
+    int* wide;
     // forward without a network: each sample's raw density interpolated
     // here from this grid (on g) instead of read from raw
     const float* density_in;
@@ -640,6 +645,7 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
         }
     }
     const float Tend = expf(kFused ? K.log_t_end : a.log_t_end_in[r]);
+    bool wide = false;   // this lane has seen a |dL/dc| out of the planes' range
     float S[5] = {Tend * a.bg[0], Tend * a.bg[1], Tend * a.bg[2], 0.0f, 0.0f};
     // auxiliary losses: the background entropy's gradient on T_end reaches
     // every sample through dT_end/dsigma_k = -delta T_end; the per-point rgb
@@ -715,6 +721,7 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
                         dc.z += ptk * w * (v[2] - tg[2]);
                     }
                     reinterpret_cast<float4*>(a.col)[s] = dc;
+                    wide |= !(fabsf(dc.x) + fabsf(dc.y) + fabsf(dc.z) < 0x1p64f);
                 }
             }
             if (a.cell_count) {   // bin the sample by fine cell (wave-uniform branch)
@@ -731,6 +738,7 @@ __device__ __forceinline__ void compose_bwd_ray(const ComposeArgs& a, int slot, 
             for (int ch = 0; ch < kCh; ++ch) S[ch] += tot[ch];
         }
     }
+    if (a.wide && __any(wide) && lane == 0) *a.wide = 1;
 }
 
 __global__ __launch_bounds__(kComposeThreads) void compose_bwd_kernel(ComposeArgs a) {
@@ -1352,6 +1360,7 @@ PrepArgs prep_args(const Common& cm, const dvgo_mlp* mlp, int* zero, int64_t nze
         P.b1 = mlp->b1;
         P.w1_in = pk.w1_in;
         P.view_col = pk.w1_ns;
+        P.wide = zero && !pk.bf16 ? reinterpret_cast<int*>(cm.ws + cm.L.wide) : nullptr;   // (a call with an adjoint)
         P.zero = zero;
         P.nzero = nzero;
         P.zblocks = zblocks;
@@ -1425,6 +1434,7 @@ MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_ke
     ma.n_kept = n_kept;
     ma.cap = cm.cap;
     ma.w1 = mlp->w1;
+    ma.w2 = mlp->w2;
     ma.b2 = mlp->precision == DVGO_BF16 ? mlp->b2 : reinterpret_cast<const float*>(cm.ws + cm.L.b2p);
     ma.w3 = mlp->w3;
     ma.b3 = mlp->b3;
@@ -1443,6 +1453,7 @@ MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_ke
     ma.partial = reinterpret_cast<float*>(cm.ws + cm.L.partial);
     ma.bf16 = mlp->precision == DVGO_BF16;
     ma.live = training && !ma.bf16 ? reinterpret_cast<uint32_t*>(cm.ws + cm.L.live) : nullptr;
+    ma.wide = training && !ma.bf16 ? reinterpret_cast<int*>(cm.ws + cm.L.wide) : nullptr;
     return ma;
 }
 
@@ -1620,6 +1631,7 @@ int32_t render_bwd_impl(const dvgo_field* field, const dvgo_mlp* mlp, const floa
     ca.cell_count = bins.cell_count;
     ca.cell_rank = bins.cell_rank;
     ca.rec_head = bins.rec_head;
+    if (mlp) ca.wide = ma.wide;
     if (fwd_compose)   // the forward compositing not yet run: both in one launch
         DVGO_LAUNCH(K_COMPOSE_BWD, compose_step_kernel, compose_grid(B), dim3(kComposeThreads), 0, s, *fwd_compose, ca);
     else

@@ -34,7 +34,7 @@ def _chain(W, b, x, order):
     return acc
 
 
-def _samples(rng, feat):
+def _samples(rng, feat, exact=True):
     """Rays along z through dyadic points of the box, and their features."""
     n = feat.shape[0]
     q = rng.integers(0, 2 * 64 - 8, (N, 3))           # position = -1 + q/64, 8 per cell
@@ -45,7 +45,7 @@ def _samples(rng, feat):
         o = np.array([c >> 2 & 1, c >> 1 & 1, c & 1])
         ii = i0 + o
         x += np.prod(np.where(o, f, 1 - f), axis=1)[:, None] * feat[ii[:, 0], ii[:, 1], ii[:, 2]]
-    assert n == 17 and np.array_equal(x, x.astype(F32))
+    assert n == 17 and (not exact or np.array_equal(x, x.astype(F32)))
     o = np.stack([-1 + q[:, 0] / 64, -1 + q[:, 1] / 64, np.full(N, -2.0)], axis=1).astype(F32)
     d = np.tile(np.array([0, 0, 1], F32), (N, 1))
     return o, d, (q[:, 2] / 8).astype(F32), x.astype(F32)

@@ -65,7 +65,7 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.scan_tmp = take(cell_scan_bytes(ncell + 1));
     L.cell_rank = take(static_cast<size_t>(cap) * 8);
     L.rec_head = take(static_cast<size_t>(cap) * 16);
-    L.rec = take(static_cast<size_t>(cap) * 64);
+    L.rec = take((static_cast<size_t>(cap) + 1) * 64);    // the last one zero (see vertex_sum)
     L.live = take(static_cast<size_t>(cap) * 32);         // ReLU branches (float32 form)
     L.step_rgb = take(static_cast<size_t>(B) * 3 * 4);    // per-ray state of dvgo_train_step
     L.step_grad = take(static_cast<size_t>(B) * 3 * 4);
@@ -174,6 +174,7 @@ struct PrepArgs {
     float* base;
     float* pe;
     int* wide;      // MlpArgs::wide, cleared (NULL: none)
+    float4* pad;    // the zero record, cleared (NULL: none)
     int* zero;      // cleared (NULL: none)
     int64_t nzero;
     int zblocks;
@@ -184,6 +185,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& P, int blk) {
     constexpr int kPackBlocks = kPackThreads / 256;
     if (blk < kPackBlocks) {
         if (blk == 0 && threadIdx.x == 0 && P.wide) *P.wide = 0;
+        if (blk == 0 && threadIdx.x < 4 && P.pad) P.pad[threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         pack_weights(P.pk, blk * 256 + threadIdx.x);
         return;
     }
@@ -792,8 +794,10 @@ struct BinArgs {
 };
 
 // Records in binned order when no network backward places them (density
-// only): the head (fractional position, dL/draw) at cell start + rank.
+// only): the head (fractional position, dL/draw) at cell start + rank.  The
+// zero record as well, which the network's preparation clears otherwise.
 __global__ __launch_bounds__(256) void bin_place_kernel(BinArgs a) {
+    if (blockIdx.x == 0 && threadIdx.x < 4) a.rec[4 * a.cap + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const int64_t n = live_count(a.n_kept, a.cap);
     for (int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; s < n;
          s += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -886,6 +890,7 @@ __device__ __forceinline__ float4 vertex_sum(const BinArgs& a, VertexRun R, Pair
     uint2* list = S.pair[lane >> 2];
     const uint32_t y0 = (1u - (part >> 1)) | (1u - (part & 1)) << 8 | 1u << 16, y1 = y0 & 0xffffu;
     const float4* rec = a.rec + part;
+    const uint32_t pad = static_cast<uint32_t>(a.cap);
     float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     bool more = R.p1 > R.p0;
     while (__any(more)) {
@@ -914,7 +919,8 @@ __device__ __forceinline__ float4 vertex_sum(const BinArgs& a, VertexRun R, Pair
                 for (int u = half * kPairsAhead / 2; u < (half + 1) * kPairsAhead / 2; ++u) {
                     const uint2 x = list[min(b + u, total - 1)];
                     y[u] = x.y;
-                    r[u] = rec[static_cast<uint64_t>(x.x) * 4];
+                    // beyond the list the zero record (a listed one times 0 is NaN where it is infinite)
+                    r[u] = rec[static_cast<uint64_t>(b + u < total ? x.x : pad) * 4];
                 }
             }
             #pragma unroll
@@ -926,8 +932,7 @@ __device__ __forceinline__ float4 vertex_sum(const BinArgs& a, VertexRun R, Pair
                     const float w0 = fabsf(r[u].x - static_cast<float>(y[u] & 255u)) *
                                      fabsf(r[u].y - static_cast<float>(y[u] >> 8 & 255u)) *
                                      fabsf(r[u].z - static_cast<float>(y[u] >> 16 & 255u));
-                    const int wb = b + u < total ? __float_as_int(w0) : 0;
-                    const float w = __int_as_float(quad_bcast<0x00>(wb));   // lane 0 holds the head
+                    const float w = __int_as_float(quad_bcast<0x00>(__float_as_int(w0)));   // lane 0 holds the head
                     acc.x += w * r[u].x;
                     acc.y += w * r[u].y;
                     acc.z += w * r[u].z;
@@ -1361,6 +1366,7 @@ PrepArgs prep_args(const Common& cm, const dvgo_mlp* mlp, int* zero, int64_t nze
         P.w1_in = pk.w1_in;
         P.view_col = pk.w1_ns;
         P.wide = zero && !pk.bf16 ? reinterpret_cast<int*>(cm.ws + cm.L.wide) : nullptr;   // (a call with an adjoint)
+        P.pad = zero ? reinterpret_cast<float4*>(cm.ws + cm.L.rec) + 4 * cm.cap : nullptr;
         P.zero = zero;
         P.nzero = nzero;
         P.zblocks = zblocks;

@@ -529,7 +529,8 @@ int32_t dvgo_proposal_bwd_adam(const float* rays_o, const float* rays_d, const f
  * are held fixed (it supervises the colours only); H's gradient is zero
  * where the clamp is active.  target [B][3]; rgb [B][3] (or NULL) receives
  * C_r; loss (device float) L; grad_density [n] and grad_rgb [n][3] are
- * ACCUMULATED (+=; the summation order varies between runs).  The adjoint
+ * ACCUMULATED with float atomics (so calls on several streams may share them;
+ * the summation order varies between runs).  The adjoint
  * walks each ray from its end with the transmittance recomputed by prefix
  * sums.  max_samples (the sampler's) at most 4096, else DVGO_E_UNSUPPORTED.
  * workspace: at least dvgo_coarse_workspace_bytes(B); with the larger

@@ -293,15 +293,14 @@ __global__ __launch_bounds__(256) void coarse_vertex_kernel(GridArgs g, const in
     const int ny = g.n[1], nz = g.n[2], cy = ny - 1, cz = nz - 1;
     const int64_t nv = static_cast<int64_t>(g.n[0]) * ny * nz;
     const int64_t v = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (v >= nv) return;
     const int k = static_cast<int>(v % nz), j = static_cast<int>((v / nz) % ny);
-    const int i = static_cast<int>(v / (static_cast<int64_t>(nz) * ny));
+    const int i = static_cast<int>(v / (static_cast<int64_t>(nz) * ny));   // (beyond the grid for v >= nv: no cells)
     int p0[4], pm[4], p1[4];   // all in flight together
     #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const int ci = i - (c >> 1), cj = j - (c & 1);
         p0[c] = pm[c] = p1[c] = 0;
-        if (ci < 0 || cj < 0 || ci >= g.n[0] - 1 || cj >= cy) continue;
+        if (v >= nv || ci < 0 || cj < 0 || ci >= g.n[0] - 1 || cj >= cy) continue;
         const int row = (ci * cy + cj) * cz;
         p0[c] = cell_start[row + (k > 0 ? k - 1 : 0)];
         pm[c] = cell_start[row + k];
@@ -323,9 +322,25 @@ __global__ __launch_bounds__(256) void coarse_vertex_kernel(GridArgs g, const in
         }
         any |= p1[c] > p0[c];
     }
-    if (!any) return;
-    grad_density[v] += acc[0];
-    for (int ch = 0; ch < 3; ++ch) grad_rgb[3 * v + ch] += acc[1 + ch];
+    const uint64_t touched = __ballot(any);
+    if (touched == 0) return;
+    // by atomics: calls on other streams may add to the same grids.  The 192
+    // colour sums of the wavefront's vertices go out in address order: as fast
+    // as plain additions (110 us for the whole call at 702k samples in 99^3
+    // cells), where three strided atomics took 10 us more.
+    __shared__ float col[4][64 * 3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (any) atomicAdd(grad_density + v, acc[0]);
+    #pragma unroll
+    for (int ch = 0; ch < 3; ++ch) col[wave][3 * lane + ch] = acc[1 + ch];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    #pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int e = 64 * u + lane;
+        if (touched >> (e / 3) & 1) atomicAdd(grad_rgb + 3 * (v - lane) + e, col[wave][e]);
+    }
 }
 
 // Single workgroup, fixed order: each thread adds every 1024th ray, eight

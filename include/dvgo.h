@@ -533,11 +533,13 @@ int32_t dvgo_proposal_bwd_adam(const float* rays_o, const float* rays_d, const f
  * the summation order varies between runs).  The adjoint
  * walks each ray from its end with the transmittance recomputed by prefix
  * sums.  max_samples (the sampler's) at most 4096, else DVGO_E_UNSUPPORTED.
- * workspace: at least dvgo_coarse_workspace_bytes(B); with the larger
- * dvgo_coarse_step_workspace_bytes(B, capacity, &field.box) (0 for an invalid
- * box), 16-byte aligned, the samples are sorted by cell and each vertex
- * gathers its gradient, without it they are scattered with float atomics,
- * several times slower. */
+ * workspace: at least dvgo_coarse_workspace_bytes(B): the samples' gradients
+ * are scattered with float atomics.  With 72 bytes more for every slot of the
+ * capacity, 9 for every cell and 4 KiB (16-byte aligned) the samples are sorted
+ * by cell and each vertex gathers its gradient.
+ * dvgo_coarse_step_workspace_bytes(B, capacity, &field.box) is the size that
+ * makes the faster choice: the first for small batches, the second for larger
+ * ones as long as it takes no more than 1 GiB (0 for an invalid box). */
 typedef struct dvgo_coarse_field {
     const float* density;
     const float* rgb;

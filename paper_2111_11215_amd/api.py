@@ -601,7 +601,11 @@ def coarse_step(density: torch.Tensor, rgb_grid: torch.Tensor, box_min, box_max,
     rgb = torch.empty((s.B, 3), dtype=torch.float32, device=dev) if want_rgb else None
     loss = torch.empty(1, dtype=torch.float32, device=dev)
     nws = lib.dvgo_coarse_step_workspace_bytes(s.B, s.capacity, ctypes.byref(f.box))
-    ws = workspace(nws, dev)
+    try:
+        ws = workspace(nws, dev)
+    except torch.cuda.OutOfMemoryError:   # the step runs in a few bytes per ray as well
+        nws = lib.dvgo_coarse_workspace_bytes(s.B)
+        ws = workspace(nws, dev)
     check("dvgo_coarse_step", lib.dvgo_coarse_step(
         ctypes.byref(f), _ptr(s.rays_o), _ptr(s.rays_d), _ptr(s.jitter), _ptr(s.t_near), _ptr(s.perm),
         _ptr(s.ray_offset), _ptr(s.sample_k), _ptr(s.n_kept), s.capacity, s.B, int(max_samples), s.step, _bg(bg),

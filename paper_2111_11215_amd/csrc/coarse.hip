@@ -469,9 +469,19 @@ size_t dvgo_coarse_workspace_bytes(int32_t B) {
     return dvgo::align_up(static_cast<size_t>(B) * 4, 256) + 256;
 }
 
+// The binned form where it is faster, and its workspace (72 bytes a slot) at
+// most 1 GiB.  It costs a fixed 35 us and 12 us per million cells, the atomics
+// 0.8 us per thousand samples more than it: with capacities of four times the
+// samples kept, 256 / 1024 rays in 39^3 cells take 36 / 36 us binned and 20 / 39
+// by atomics, 256 / 512 / 1024 rays in 99^3 48 / 53 / 57 and 40 / 51 / 87, in
+// 127^3 60 / 64 / 72 and 48 / 63 / 113.
 size_t dvgo_coarse_step_workspace_bytes(int32_t B, int64_t capacity, const dvgo_box* grid) {
     if (B < 0 || capacity < 0 || !dvgo::box_ok(grid, 2)) return 0;
-    return coarse_ws(B, capacity, coarse_cells(*grid)).total;
+    const size_t small = dvgo_coarse_workspace_bytes(B);
+    const int64_t ncell = coarse_cells(*grid);
+    if (capacity < 100000 + ncell / 40 * 3 || capacity >= (1LL << 31)) return small;
+    const size_t binned = coarse_ws(B, capacity, ncell).total;
+    return binned - small <= (1ull << 30) ? binned : small;
 }
 
 int32_t dvgo_coarse_step(const dvgo_coarse_field* field, const float* rays_o, const float* rays_d,

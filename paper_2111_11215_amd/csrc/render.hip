@@ -989,7 +989,12 @@ struct GridAdamArgs {
 // their densities and features (and their bfloat16 copy), each lane on the
 // values it has summed; a vertex no sample touches takes the step with a zero
 // gradient, as dense Adam does.  The gradient never reaches memory.  A
-// wavefront's 16 vertices own 768 consecutive bytes of each feature stream.
+// wavefront's 16 vertices own 768 consecutive bytes of each feature stream,
+// six whole lines, which go past the caches; of a density stream they own half
+// a line, which is left to the L2 to join with the neighbour's (past the caches
+// as well, a grid that few samples touch took longer than with 64 vertices per
+// wavefront: 128 rays in 255^3 cells 718 us against 595, now 667; 64 rays in
+// 189^3 279, 260, 254; 512 rays in 147^3 145, 132, 133).
 //
 // With an activity mask, a vertex whose bit is clear (both moments zero)
 // and that no sample touches is skipped: its step would compute m = v = 0
@@ -1066,9 +1071,9 @@ __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAda
                 mq = __builtin_nontemporal_load(M + at);
                 vq = __builtin_nontemporal_load(V + at);
             } else {
-                pq[3] = __builtin_nontemporal_load(o.pd + v);
-                mq[3] = __builtin_nontemporal_load(o.md + v);
-                vq[3] = __builtin_nontemporal_load(o.vd + v);
+                pq[3] = o.pd[v];
+                mq[3] = o.md[v];
+                vq[3] = o.vd[v];
             }
         }
         float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -1096,9 +1101,9 @@ __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAda
                     __builtin_nontemporal_store(bv, shadow + at);
                 }
             } else {
-                __builtin_nontemporal_store(pq[3], o.pd + v);
-                __builtin_nontemporal_store(mq[3], o.md + v);
-                __builtin_nontemporal_store(vq[3], o.vd + v);
+                o.pd[v] = pq[3];
+                o.md[v] = mq[3];
+                o.vd[v] = vq[3];
             }
         }
         if (active && __any(touched)) {   // (bits are only ever set)
@@ -1320,12 +1325,15 @@ int32_t grid_adam_args(const dvgo_grid_adam* opt, GridAdamArgs* o) {
     return DVGO_OK;
 }
 
-// Workgroups of the fused grid Adam: a multiple of 8 (one share per XCD),
-// 6 per compute unit (as many as its registers let be resident), no more than
-// the vertices need.
+// Workgroups of the fused grid Adam: a multiple of 8 (one share per XCD), no
+// more than the vertices need; 6 per compute unit (as many as its registers let
+// be resident), 16 from 2^23 vertices on, where an uneven grid is dealt more
+// evenly in smaller shares (6 and 16 per compute unit: 682 and 667 us for 128
+// rays in 255^3 cells, 1483 and 1458 for 32768; 254 and 257 for 64 rays in
+// 189^3, 182 and 190 for 8192 in 159^3).
 int grid_adam_blocks(int64_t nv) {
     const int64_t per_xcd = (nv + 8 * 64 - 1) / (8 * 64);
-    int64_t b = static_cast<int64_t>(dvgo::device_cu_count()) * 6 / 8;
+    int64_t b = static_cast<int64_t>(dvgo::device_cu_count()) * (nv < (1 << 23) ? 6 : 16) / 8;
     if (b > per_xcd) b = per_xcd;
     if (b < 1) b = 1;
     return static_cast<int>(8 * b);

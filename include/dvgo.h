@@ -263,10 +263,14 @@ int32_t dvgo_sample_rays_noalloc(const float* rays_o, const float* rays_d, const
  * bg: host float[3].
  * workspace: dvgo_render_workspace_bytes(B, capacity, channels, &field.box)
  *   bytes (0 for an unsupported channel count or an invalid box), which the
- *   backward needs; the forward alone needs only the smaller
+ *   backward of a float32 network needs; the backward of a bfloat16 one, or
+ *   without a network, needs 32 bytes per slot of the capacity less,
+ *   dvgo_render_bf16_workspace_bytes; the forward alone needs only the smaller
  *   dvgo_render_fwd_workspace_bytes. */
 size_t dvgo_render_workspace_bytes(int32_t B, int64_t capacity, int32_t channels,
                                    const dvgo_box* grid /*host*/);
+size_t dvgo_render_bf16_workspace_bytes(int32_t B, int64_t capacity, int32_t channels,
+                                        const dvgo_box* grid /*host*/);
 size_t dvgo_render_fwd_workspace_bytes(int32_t B, int64_t capacity, int32_t channels,
                                        const dvgo_box* grid /*host*/);
 int32_t dvgo_render_fwd(const dvgo_field* field /*host*/, const dvgo_mlp* mlp /*host or NULL*/,

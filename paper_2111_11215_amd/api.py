@@ -271,6 +271,14 @@ def _bg(bg):
     return arr
 
 
+def _render_bytes(lib, s: Samples, field: Field, mlp: Optional[Mlp]) -> int:
+    """Workspace of a render and its backward (the same for both, so that the
+    second finds the first's)."""
+    f32 = mlp is not None and mlp.precision == DVGO_F32
+    size = lib.dvgo_render_workspace_bytes if f32 else lib.dvgo_render_bf16_workspace_bytes
+    return size(s.B, s.capacity, CHANNELS, ctypes.byref(field.box))
+
+
 def render_fwd(grid: Grid, mlp_flat: Optional[torch.Tensor], s: Samples, bg=(1.0, 1.0, 1.0),
                precision: int = DVGO_F32, use_shadow: bool = False, want_seg_w: bool = False,
                want_sample_w: bool = False, want_depth_acc: bool = True) -> dict:
@@ -287,7 +295,7 @@ def render_fwd(grid: Grid, mlp_flat: Optional[torch.Tensor], s: Samples, bg=(1.0
         "seg_w": torch.empty((B, NSEG), dtype=torch.float32, device=dev) if want_seg_w else None,
         "sample_w": torch.empty(max(s.capacity, 1), dtype=torch.float32, device=dev) if want_sample_w else None,
     }
-    nws = lib.dvgo_render_workspace_bytes(B, s.capacity, CHANNELS, ctypes.byref(field.box))
+    nws = _render_bytes(lib, s, field, mlp)
     ws = workspace(nws, dev)
     check("dvgo_render_fwd", lib.dvgo_render_fwd(
         ctypes.byref(field), ctypes.byref(mlp) if mlp is not None else None, _ptr(s.rays_o), _ptr(s.rays_d),
@@ -307,7 +315,7 @@ def render_bwd(grid: Grid, mlp_flat: Optional[torch.Tensor], s: Samples, log_t_e
     dev = s.rays_o.device
     field = grid.field(use_shadow)
     mlp = mlp_struct(mlp_flat, precision) if mlp_flat is not None else None
-    nws = lib.dvgo_render_workspace_bytes(s.B, s.capacity, CHANNELS, ctypes.byref(field.box))
+    nws = _render_bytes(lib, s, field, mlp)
     ws = workspace(nws, dev)
     check("dvgo_render_bwd", lib.dvgo_render_bwd(
         ctypes.byref(field), ctypes.byref(mlp) if mlp is not None else None, _ptr(s.rays_o), _ptr(s.rays_d),
@@ -353,7 +361,7 @@ def render_bwd_adam(grid: Grid, mlp_flat: torch.Tensor, s: Samples, log_t_end: t
     field = grid.field(use_shadow)
     mlp = mlp_struct(mlp_flat, precision)
     opt = _grid_adam(grid, density_m, density_v, feat_m, feat_v, lr, t, betas, eps, active)
-    nws = lib.dvgo_render_workspace_bytes(s.B, s.capacity, CHANNELS, ctypes.byref(field.box))
+    nws = _render_bytes(lib, s, field, mlp)
     ws = workspace(nws, dev)
     check("dvgo_render_bwd_adam", lib.dvgo_render_bwd_adam(
         ctypes.byref(field), ctypes.byref(mlp), _ptr(s.rays_o), _ptr(s.rays_d), _ptr(s.jitter), _ptr(s.t_near),
@@ -386,7 +394,7 @@ def train_step(grid: Grid, mlp_flat: torch.Tensor, s: Samples, target: torch.Ten
                         int(t_net))
     rgb = torch.empty((s.B, 3), dtype=torch.float32, device=dev) if want_rgb else None
     loss = torch.empty(1, dtype=torch.float32, device=dev)
-    nws = lib.dvgo_render_workspace_bytes(s.B, s.capacity, CHANNELS, ctypes.byref(field.box))
+    nws = _render_bytes(lib, s, field, mlp)
     ws = workspace(nws, dev)
     check("dvgo_train_step", lib.dvgo_train_step(
         ctypes.byref(field), ctypes.byref(mlp), _ptr(s.rays_o), _ptr(s.rays_d), _ptr(s.jitter), _ptr(s.t_near),

@@ -33,7 +33,7 @@ constexpr int kMaxBwdBlocks = 256;
 
 struct WsLayout {
     size_t base, pe, w1p, w2p, b2p, w1pb, w2pb, w2tpb, w3pb, w3tpb, w1tpb, raw, feat, col, partial, wide, cell_count,
-        cell_start, scan_tmp, cell_rank, rec_head, rec, live, step_rgb, step_grad, step_logt, step_sqerr, total;
+        cell_start, scan_tmp, cell_rank, rec_head, rec, step_rgb, step_grad, step_logt, step_sqerr, live, total;
 };
 
 WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
@@ -66,11 +66,11 @@ WsLayout ws_layout(int64_t B, int64_t cap, int64_t ncell) {
     L.cell_rank = take(static_cast<size_t>(cap) * 8);
     L.rec_head = take(static_cast<size_t>(cap) * 16);
     L.rec = take((static_cast<size_t>(cap) + 1) * 64);    // the last one zero (see vertex_sum)
-    L.live = take(static_cast<size_t>(cap) * 32);         // ReLU branches (float32 form)
     L.step_rgb = take(static_cast<size_t>(B) * 3 * 4);    // per-ray state of dvgo_train_step
     L.step_grad = take(static_cast<size_t>(B) * 3 * 4);
     L.step_logt = take(static_cast<size_t>(B) * 4);
     L.step_sqerr = take(static_cast<size_t>(B) * 4);
+    L.live = take(static_cast<size_t>(cap) * 32);         // ReLU branches: the float32 network's adjoint only, so last
     L.total = off;
     return L;
 }
@@ -1291,7 +1291,9 @@ int32_t validate(const dvgo_field* field, const dvgo_mlp* mlp, const float* rays
     if (!n_kept) return DVGO_E_ARG;
     if (capacity > 0 && (!sample_ray || !sample_k)) return DVGO_E_ARG;
     const size_t need = forward_only ? dvgo_render_fwd_workspace_bytes(B, capacity, kC, &field->box)
-                                     : dvgo_render_workspace_bytes(B, capacity, kC, &field->box);
+                        : mlp && mlp->precision == DVGO_F32
+                            ? dvgo_render_workspace_bytes(B, capacity, kC, &field->box)
+                            : dvgo_render_bf16_workspace_bytes(B, capacity, kC, &field->box);
     if (workspace_bytes < need || (!workspace && workspace_bytes)) return DVGO_E_CAPACITY;
     return DVGO_OK;
 }
@@ -1702,6 +1704,11 @@ int64_t dvgo_mlp_param_count(int32_t channels, int32_t hidden, int32_t pe_x) {
 size_t dvgo_render_workspace_bytes(int32_t B, int64_t capacity, int32_t channels, const dvgo_box* grid) {
     if (B < 0 || capacity < 0 || channels != kC || !dvgo::box_ok(grid, 2)) return 0;
     return ws_layout(B, capacity, cell_count_of(*grid)).total;
+}
+
+size_t dvgo_render_bf16_workspace_bytes(int32_t B, int64_t capacity, int32_t channels, const dvgo_box* grid) {
+    if (B < 0 || capacity < 0 || channels != kC || !dvgo::box_ok(grid, 2)) return 0;
+    return ws_layout(B, capacity, cell_count_of(*grid)).live;
 }
 
 // The forward uses the front of the layout only: per-ray encodings, packed

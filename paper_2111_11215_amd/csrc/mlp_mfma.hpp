@@ -4,15 +4,18 @@
 //
 // Layout.  A 32x32 accumulator tile of v_mfma_f32_32x32x16_bf16 holds, in
 // lane l and register r, row 8*(r/4) + 4*(l/32) + (r%4) and column l%32.
-// Activations are kept transposed ("feature rows, sample columns"): a wave
-// owns 32 samples (one per lane column) and each lane holds 16 features per
-// 32-feature tile.  The next layer consumes those registers directly as its
-// B operand; the K order this implies is folded into the packed weights
-// (phi() below), so a layer chain never leaves registers.  Weight gradients
-// need the sample index as the contraction dimension, so the activations of
-// a workgroup's 128 samples are staged through LDS once per block and each
-// wave accumulates its own slice of dW in registers across the whole
-// persistent loop; per-workgroup partials are summed afterwards.
+// Activations are kept transposed ("feature rows, sample columns").  In the
+// forward a wave owns 32 samples (one per lane column) and each lane holds 16
+// features per 32-feature tile; the next layer consumes those registers
+// directly as its B operand; the K order this implies is folded into the
+// packed weights (phi16 below), so a layer chain never leaves registers.  In
+// the adjoint the weights stay and a block's samples pass: a wave owns 32
+// features of every layer, and the activations go between the waves as
+// [sample][feature] rows in LDS in the same K order.  Weight gradients need the
+// sample index as the contraction dimension: they read those rows through the
+// LDS transpose load, and each wave accumulates its own slice of dW in
+// registers across the whole persistent loop; per-workgroup partials are
+// summed afterwards.
 #pragma once
 
 #include "common.hpp"
@@ -164,8 +167,7 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
         // float32: index ((mt*16 + q)*64 + lane)*4 + u, step st = 4q + u
         const int u = gid & 3, lane = (gid >> 2) & 63, q = (gid >> 8) & 15, mt = gid >> 12;
         const int st = 4 * q + u, m = lane & 31, h = lane >> 5;
-        const int row = 32 * mt + m, kk = phi32(st, h);
-        a.w2p[gid] = a.w2[row * kH + kk];
+        if (!a.bf16) a.w2p[gid] = a.w2[(32 * mt + m) * kH + phi32(st, h)];
         {
             // bfloat16 planes: index ((mt*8 + st)*64 + lane)*8 + i
             const int i = gid & 7, lane2 = (gid >> 3) & 63, st2 = (gid >> 9) & 7, mt2 = gid >> 12;
@@ -175,7 +177,7 @@ __device__ __forceinline__ void pack_weights(const PackArgs& a, int gid) {
             store_planes(a.w2tpb, gid, kW2PackBF16, a.w2[k2 * kH + row2], planes);
         }
     }
-    if (gid < 4 * a.w1_q * 64 * 4) {
+    if (!a.bf16 && gid < 4 * a.w1_q * 64 * 4) {
         // float32 layer 1: index ((mt*Q + q)*64 + lane)*4 + u, st = 4q+u, k = 2st + h (< w1_ns)
         const int u = gid & 3, lane = (gid >> 2) & 63, q = (gid >> 8) % a.w1_q, mt = (gid >> 8) / a.w1_q;
         const int st = 4 * q + u, m = lane & 31, h = lane >> 5;
@@ -236,7 +238,6 @@ struct MlpArgs {
     const int* cell_start;    // [ncell + 1]
     const float4* rec_head;   // [cap] (fx, fy, fz, dL/draw)
     float4* rec;              // [cap][4] binned records
-    int nrays;                // rows of base and pe
     uint32_t* live;           // [cap][8] ReLU branches (float32 form; NULL: not wanted)
     int* wide;                // float32 adjoint: not 0 where its values may leave the planes' range
 };
@@ -255,11 +256,6 @@ struct PosArgs {
     float pe_c[3];
     float pe_ih[3];
 };
-
-__device__ __forceinline__ float4* binned_record(const MlpArgs& a, int64_t s) {
-    const int2 cr = a.cell_rank[s];
-    return a.rec + (static_cast<int64_t>(a.cell_start[cr.x]) + cr.y) * 4;
-}
 
 __device__ __forceinline__ MlpArgs refresh(const MlpArgs& a) {
     MlpArgs l = a;
@@ -621,8 +617,12 @@ __device__ __forceinline__ T lds_get(uint32_t a) { return *(__attribute__((addre
 template <typename T>
 __device__ __forceinline__ void lds_put(uint32_t a, const T& v) { *(__attribute__((address_space(3))) T*)a = v; }
 
-// K-major operand from two LDS transpose reads (rows r and r + 4 of a lane's
-// samples): see tr_operand for the lanes' roles.
+// K-major operand from two LDS transpose reads: lane (m, h) receives feature
+// c0 + m of samples s0 + 8h .. s0 + 8h + 7.  A read transposes a 16x4 block
+// within each group of 16 lanes: lane t of group G addresses sample
+// s0 + 8(G/2) + t/4 and features c0 + 16(G%2) + 4(t%4) .. + 3, and receives
+// feature c0 + 16(G%2) + t of those four samples.  a: the first four samples'
+// address, b: the same 4 rows on.
 __device__ __forceinline__ bf16x8 tr_pair(uint32_t a, uint32_t b) {
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a);

@@ -1,14 +1,15 @@
 // The colour network's float32 form on the bfloat16 matrix cores.
 //
 // A float32 value is the exact sum of three bfloat16 values (planes hi, mid,
-// lo: 8 bits of significand each, see store_planes), so a product of two
+// lo: 8 bits of significand each, see store_planes; the splitting of a wide
+// float into narrow ones goes back to Dekker, 1971), so a product of two
 // float32 values is the sum of nine bfloat16 products, each exact in the
 // matrix core's float32 accumulation.  Six of them are taken, hi*hi, hi*mid,
-// mid*hi, mid*mid, hi*lo and lo*hi; the three left out are below 2^-26 of the
-// product, a quarter of a float32 rounding.  Six K = 16 bfloat16 instructions
-// replace eight K = 2 float32 ones of twice their duration: 2.7 times the
-// rate, and 48 roundings of an accumulator over a 128-wide layer instead of
-// 64.
+// mid*hi, mid*mid, hi*lo and lo*hi; the three left out are at most 2^-24 of the
+// product, half a unit in float32's last place, and 2^-27.4 rms.  Six K = 16
+// bfloat16 instructions replace eight K = 2 float32 ones of twice their
+// duration: 2.7 times the rate, and 48 roundings of an accumulator over a
+// 128-wide layer instead of 64.
 //
 // Range: below about 2^-110 the low plane loses bits to underflow (an error of
 // less than 2^-130).  Above the largest bfloat16 the high plane is infinite and

@@ -8,7 +8,8 @@
 //   prep     pack the network weights into matrix-core operand order;
 //            per-ray view encoding PE(d) and the first layer's per-ray part
 //   gather   trilinear density and feature interpolation per sample
-//   mlp      colour network on float32 (or bfloat16) matrix cores
+//   mlp      colour network on the bfloat16 matrix cores (float32 operands
+//            as three bfloat16 planes)
 //   compose  per-ray front-to-back compositing with wavefront prefix scans
 // and the backward pass adds
 //   compose' walk each ray from its end (suffix scans from log_t_end)
@@ -276,8 +277,6 @@ struct GatherArgs {
     GridArgs g;
     const float* density;
     const void* feat;
-    int feat_bf16;
-    int with_feat;
     const int64_t* n_kept;
     int64_t cap;
     float* raw_out;
@@ -383,8 +382,7 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int blk, int nb
     }
 }
 
-template <int kFeat>
-__global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) { gather_body<kFeat>(a, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void density_gather_kernel(GatherArgs a) { gather_body<0>(a, blockIdx.x, gridDim.x); }
 
 // The gather and the per-call preparation in one launch (the two are
 // independent: the preparation's workgroups fill the gather's latency-bound
@@ -1398,14 +1396,12 @@ int32_t run_prep(const Common& cm, const dvgo_mlp* mlp, hipStream_t s, int* zero
     return DVGO_OK;
 }
 
-GatherArgs gather_args(const Common& cm, const dvgo_field* field, bool with_feat, const int64_t* n_kept) {
+GatherArgs gather_args(const Common& cm, const dvgo_field* field, const int64_t* n_kept) {
     GatherArgs ga;
     ga.sa = cm.sa;
     ga.g = cm.g;
     ga.density = field->density;
     ga.feat = field->feat;
-    ga.feat_bf16 = field->feat_dtype == DVGO_BF16;
-    ga.with_feat = with_feat;
     ga.n_kept = n_kept;
     ga.cap = cm.cap;
     ga.raw_out = reinterpret_cast<float*>(cm.ws + cm.L.raw);
@@ -1415,14 +1411,10 @@ GatherArgs gather_args(const Common& cm, const dvgo_field* field, bool with_feat
 
 int gather_blocks(const Common& cm) { return grid_for(cm.cap, 256, dvgo::device_cu_count() * 16); }
 
-int32_t run_gather(const Common& cm, const dvgo_field* field, bool with_feat, const int64_t* n_kept,
-                   hipStream_t s) {
+int32_t run_density_gather(const Common& cm, const dvgo_field* field, const int64_t* n_kept, hipStream_t s) {
     if (cm.cap == 0) return DVGO_OK;
-    const GatherArgs ga = gather_args(cm, field, with_feat, n_kept);
-    const int blocks = gather_blocks(cm);
-    if (!with_feat) DVGO_LAUNCH(K_GATHER, gather_kernel<0>, dim3(blocks), dim3(256), 0, s, ga);
-    else if (!ga.feat_bf16) DVGO_LAUNCH(K_GATHER, gather_kernel<1>, dim3(blocks), dim3(256), 0, s, ga);
-    else DVGO_LAUNCH(K_GATHER, gather_kernel<2>, dim3(blocks), dim3(256), 0, s, ga);
+    DVGO_LAUNCH(K_GATHER, density_gather_kernel, dim3(gather_blocks(cm)), dim3(256), 0, s,
+                gather_args(cm, field, n_kept));
     return dvgo::launch_status();
 }
 
@@ -1432,20 +1424,19 @@ int32_t run_prep_gather(const Common& cm, const dvgo_mlp* mlp, const dvgo_field*
                         hipStream_t s, int* zero = nullptr, int64_t nzero = 0) {
     if (!mlp || cm.cap == 0) {
         if (int32_t st = run_prep(cm, mlp, s, zero, nzero)) return st;
-        return run_gather(cm, field, mlp != nullptr, n_kept, s);
+        return run_density_gather(cm, field, n_kept, s);
     }
     const PrepArgs P = prep_args(cm, mlp, zero, nzero);
-    const GatherArgs ga = gather_args(cm, field, true, n_kept);
+    const GatherArgs ga = gather_args(cm, field, n_kept);
     const int gb = gather_blocks(cm);
     const dim3 grid(static_cast<unsigned>(gb + P.blocks));
-    if (ga.feat_bf16) DVGO_LAUNCH(K_GATHER, prep_gather_kernel<2>, grid, dim3(256), 0, s, P, ga, gb);
+    if (field->feat_dtype == DVGO_BF16) DVGO_LAUNCH(K_GATHER, prep_gather_kernel<2>, grid, dim3(256), 0, s, P, ga, gb);
     else DVGO_LAUNCH(K_GATHER, prep_gather_kernel<1>, grid, dim3(256), 0, s, P, ga, gb);
     return dvgo::launch_status();
 }
 
 MlpArgs make_mlp_args(const Common& cm, const dvgo_mlp* mlp, const int64_t* n_kept, bool training) {
     MlpArgs ma;
-    ma.nrays = cm.B;
     ma.sample_ray = cm.sa.sample_ray;
     ma.n_kept = n_kept;
     ma.cap = cm.cap;
@@ -1557,7 +1548,7 @@ Bins bins_of(const Common& cm, const dvgo_field* field) {
 }
 
 // Records placed in binned order (by the network backward, or here when
-// there is none), then one thread per vertex: gradient into the grids, or
+// there is none), then a lane quad per vertex: gradient into the grids, or
 // the grids' fused Adam step.
 int32_t run_vertex(const Common& cm, const dvgo_field* field, const Bins& b, bool with_feat, bool place,
                    const int64_t* n_kept, float* grad_density, float* grad_feat, const GridAdamArgs* opt,

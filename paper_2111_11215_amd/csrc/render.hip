@@ -983,6 +983,11 @@ struct GridAdamArgs {
     dvgo::AdamCoef c;
 };
 
+// Vertices of a chunk: what an XCD takes at a time (two x-planes).
+__host__ __device__ inline int64_t adam_chunk(int ny, int nz) {
+    return (2 * static_cast<int64_t>(ny) * nz + 255) / 256 * 256;
+}
+
 // The vertices' gradients as in vertex_gather_kernel, then the Adam step of
 // their densities and features (and their bfloat16 copy), each lane on the
 // values it has summed; a vertex no sample touches takes the step with a zero
@@ -1022,7 +1027,7 @@ __device__ __forceinline__ void vertex_adam_body(const BinArgs& a, const GridAda
     // an XCD walk its chunks in 64-vertex steps.  gridDim.x is a multiple of
     // 8; every wave's first vertex is a multiple of 16, so a wave owns a
     // half word of the activity mask.
-    const int64_t kChunk = (2 * static_cast<int64_t>(ny) * nz + 255) / 256 * 256;
+    const int64_t kChunk = adam_chunk(ny, nz);
     const int xcd = blk & 7, nloc = nblk >> 3, loc = blk >> 3;
     const int64_t nchunk = (nv + kChunk - 1) / kChunk;
     const int64_t mine = nchunk > xcd ? (nchunk - xcd + 7) / 8 : 0;   // chunks of this XCD
@@ -1326,13 +1331,19 @@ int32_t grid_adam_args(const dvgo_grid_adam* opt, GridAdamArgs* o) {
 }
 
 // Workgroups of the fused grid Adam: a multiple of 8 (one share per XCD), no
-// more than the vertices need; 6 per compute unit (as many as its registers let
-// be resident), 16 from 2^23 vertices on, where an uneven grid is dealt more
-// evenly in smaller shares (6 and 16 per compute unit: 682 and 667 us for 128
-// rays in 255^3 cells, 1483 and 1458 for 32768; 254 and 257 for 64 rays in
-// 189^3, 182 and 190 for 8192 in 159^3).
-int grid_adam_blocks(int64_t nv) {
-    const int64_t per_xcd = (nv + 8 * 64 - 1) / (8 * 64);
+// more than the XCD with the most chunks has steps of 64 vertices (by the
+// vertices of an even share, a small grid, whose chunks do not reach all XCDs,
+// was walked by an eighth of the workgroups it can use: a training step of 4096
+// rays in 7^3 cells 472 us, now 189; 8192 in 11^3 282 and 189, in 23^3 151 and
+// 129); 6 per compute unit (as many as its registers let be resident), 16 from
+// 2^23 vertices on, where an uneven grid is dealt more evenly in smaller shares
+// (6 and 16 per compute unit: 682 and 667 us for 128 rays in 255^3 cells, 1483
+// and 1458 for 32768; 254 and 257 for 64 rays in 189^3, 182 and 190 for 8192 in
+// 159^3).
+int grid_adam_blocks(const GridArgs& g) {
+    const int64_t nv = static_cast<int64_t>(g.n[0]) * g.n[1] * g.n[2], chunk = adam_chunk(g.n[1], g.n[2]);
+    const int64_t nchunk = (nv + chunk - 1) / chunk;
+    const int64_t per_xcd = (nchunk + 7) / 8 * (chunk / 64);
     int64_t b = static_cast<int64_t>(dvgo::device_cu_count()) * (nv < (1 << 23) ? 6 : 16) / 8;
     if (b > per_xcd) b = per_xcd;
     if (b < 1) b = 1;
@@ -1574,11 +1585,11 @@ int32_t run_vertex(const Common& cm, const dvgo_field* field, const Bins& b, boo
     }
     const int64_t nv = static_cast<int64_t>(field->box.n[0]) * field->box.n[1] * field->box.n[2];
     if (opt && red) {
-        const int vb = grid_adam_blocks(nv);
+        const int vb = grid_adam_blocks(ba.g);
         DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_reduce_kernel, dim3(vb + (red->nparams + 63) / 64), dim3(256), 0, s, ba,
                     *opt, vb, *red);
     } else if (opt)
-        DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_kernel, dim3(grid_adam_blocks(nv)), dim3(256), 0, s, ba, *opt);
+        DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_kernel, dim3(grid_adam_blocks(ba.g)), dim3(256), 0, s, ba, *opt);
     else
         DVGO_LAUNCH(K_SCATTER, vertex_gather_kernel, dim3(grid_for(nv, 64, cus * 16)), dim3(256), 0, s, ba);
     return dvgo::launch_status();
@@ -1607,9 +1618,7 @@ int32_t render_bwd_impl(const dvgo_field* field, const dvgo_mlp* mlp, const floa
         // no samples: every vertex still takes its zero-gradient Adam step
         BinArgs ba{};
         ba.g = dvgo::make_grid(field->box);
-        const int64_t nv = static_cast<int64_t>(field->box.n[0]) * field->box.n[1] * field->box.n[2];
-        DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_kernel, dim3(grid_adam_blocks(nv)), dim3(256),
-                    0, s, ba, *opt);
+        DVGO_LAUNCH(K_GRID_ADAM, vertex_adam_kernel, dim3(grid_adam_blocks(ba.g)), dim3(256), 0, s, ba, *opt);
         return dvgo::launch_status();
     }
     Common cm = make_common(field, rays_o, rays_d, jitter, t_near, sample_ray, sample_k, capacity, B, step,

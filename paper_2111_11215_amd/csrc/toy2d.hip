@@ -127,16 +127,16 @@ __device__ __forceinline__ void toy_loss(const float* __restrict__ part, int n, 
     if (threadIdx.x == 0) *loss = red[0] * inv_n;
 }
 
-// dL/dV[a][b] by a group of kSide x kSide lanes.  The vertex's pixels are
+// dL/dV[a][b] by a group of kRows x kCols lanes.  The vertex's pixels are
 // those whose u, v lie within one cell of it: lane (r, c) of the group takes
-// every kSide-th row and column of that window (widened by the rounding of u
+// every kRows-th row and kCols-th column of that window (widened by the rounding of u
 // and v; each pixel's own cell decides), and the lanes' sums meet in a fixed
 // butterfly, so the result does not depend on scheduling.  Latency-bound: the
 // pixel kernel's factor is read here, where it was evaluated again for every
 // pixel of a window that a whole wavefront walked, 24 -> 4.6 us for a
 // 128 x 128 grid over 256 x 256 pixels (16 pixels a vertex).  The last workgroup
 // takes the loss, which had a launch of its own (4 us).
-template <int kSide>
+template <int kRows, int kCols>
 __global__ __launch_bounds__(256) void toy_vertex_kernel(ToyArgs a, const float* __restrict__ factor,
                                                          float* __restrict__ grad, const float* __restrict__ part,
                                                          int nparts, float inv_n, float* __restrict__ loss) {
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void toy_vertex_kernel(ToyArgs a, const float*
         toy_loss(part, nparts, inv_n, loss);
         return;
     }
-    constexpr int kLanes = kSide * kSide;
+    constexpr int kLanes = kRows * kCols;
     const int64_t nv = static_cast<int64_t>(a.gh) * a.gw;
     const int l = threadIdx.x % kLanes;
     const int64_t vid = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / kLanes;
@@ -160,8 +160,8 @@ __global__ __launch_bounds__(256) void toy_vertex_kernel(ToyArgs a, const float*
     const int j_lo = max(0, static_cast<int>(floorf((vb - 1) * cols_per - mj)));
     const int j_hi = min(a.W - 1, static_cast<int>(ceilf((vb + 1) * cols_per + mj - 1.0f)) - 1);
     float g = 0.0f;
-    for (int i = i_lo + l / kSide; i <= i_hi; i += kSide)
-        for (int j = j_lo + l % kSide; j <= j_hi; j += kSide) {
+    for (int i = i_lo + l / kCols; i <= i_hi; i += kRows)
+        for (int j = j_lo + l % kCols; j <= j_hi; j += kCols) {
             const Bil b = bilinear(a, i, j);
             const int di = va - b.i0, dj = vb - b.j0;
             const float w = di == 0 ? (dj == 0 ? b.w[0] : b.w[1]) : (dj == 0 ? b.w[2] : b.w[3]);
@@ -239,15 +239,21 @@ int32_t dvgo_toy2d_loss_grad(const float* V, int32_t gh, int32_t gw, const float
     // 4 x 4 lanes a vertex, or 8 x 8 where it has more than 16 pixels (a stride
     // above 4).  16 and 64 lanes on a 256 x 256 image, launch included: 6.2 and
     // 9.1 us at stride 2, 6.9 and 6.3 at 4, 7.7 and 6.3 at 6, 12.8 and 10.0 at 16;
-    // on 512 x 512, 10.9 and 21.1 at 2, 7.3 and 10.8 at 4, 15.3 and 9.3 at 16
-    const bool wide = static_cast<int64_t>(H) * W > 16 * nv;
+    // on 512 x 512, 10.9 and 21.1 at 2, 7.3 and 10.8 at 4, 15.3 and 9.3 at 16.
+    // A window of more than 256 pixels, 16 times as long as wide, takes its 64
+    // lanes along it: the call and an Adam step 62 us by 4 x 4 and 22 by 1 x 64
+    // for a 4 x 2048 image over a 256 x 4 grid, 78 and 23 for its transpose; not
+    // shorter ones, where many vertices have a row or none (a stride of 34, 2 x
+    // 4096 over 3000 x 120: 56 us by 4 x 4 and 88 by 1 x 64)
+    const double rows = static_cast<double>(H) / (gh - 1), cols = static_cast<double>(W) / (gw - 1);
+    const bool along = cols > 128.0 && cols > 16.0 * rows, down = rows > 128.0 && rows > 16.0 * cols;
+    const bool wide = along || down || static_cast<int64_t>(H) * W > 16 * nv;
     const int64_t blocks = (nv * (wide ? 64 : 16) + 255) / 256 + 1;
     const float inv_n = 1.0f / static_cast<float>(n);
-    const dim3 grid(static_cast<unsigned>(blocks));
-    if (wide)
-        DVGO_LAUNCH(K_TOY_VERTEX, toy_vertex_kernel<8>, grid, dim3(256), 0, s, a, dalpha, grad, part, nblk, inv_n, loss);
-    else
-        DVGO_LAUNCH(K_TOY_VERTEX, toy_vertex_kernel<4>, grid, dim3(256), 0, s, a, dalpha, grad, part, nblk, inv_n, loss);
+    const auto kernel = along ? toy_vertex_kernel<1, 64> : down ? toy_vertex_kernel<64, 1>
+                        : wide ? toy_vertex_kernel<8, 8> : toy_vertex_kernel<4, 4>;
+    DVGO_LAUNCH(K_TOY_VERTEX, kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a, dalpha, grad, part, nblk,
+                inv_n, loss);
     return dvgo::launch_status();
 }
 

@@ -133,6 +133,7 @@ SIGNATURES = {
     "dvgo_profile_read": (c_int32, [POINTER(ctypes.c_double), POINTER(c_int64)]),
 }
 
+# (toy_reduce keeps its number: the loss is summed by toy_vertex's launch)
 KERNEL_IDS = {name: i for i, name in enumerate([
     "ray_setup", "morton_sort", "count_kept", "scan", "fill_kept", "coarse_mask", "pack", "ray_base", "gather",
     "mlp_fwd", "compose_fwd", "compose_bwd", "mlp_bwd", "scatter", "reduce", "photo_loss", "adam", "prop_fwd",

@@ -818,8 +818,8 @@ __global__ __launch_bounds__(256) void bin_place_kernel(BinArgs a) {
 // instructions with 9 of 64 lanes active: the address units, busy 72 % of the
 // time, bounded the walk.  With the Adam step: 106k samples in 31^3 cells
 // 34 -> 17 us, 153k in 99^3 65 -> 57, 387k in 159^3 183 -> 175, 7.1M in 255^3
-// 1600 -> 1494 (5.7 GB of parameters and moments are 1040 us); the plain
-// gather in 127^3 cells 70 -> 53.  Eight records ahead in fewer wavefronts:
+// 1600 -> 1494 (1460 in the shares of grid_adam_blocks; 5.7 GB of parameters
+// and moments are 1040 us); the plain gather in 127^3 cells 70 -> 53.  Eight records ahead in fewer wavefronts:
 // 14.5, 58, 191, 1520 us.  Four vertices per quad, their sums through LDS,
 // take fewer loads (7.1M samples 1390 us) but a quarter of the wavefronts: 57
 // us for the first of these.  Sums by LDS float atomics, in any split, were slower than

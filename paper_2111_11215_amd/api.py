@@ -39,10 +39,13 @@ _WS: dict = {}
 
 def workspace(nbytes: int, device) -> torch.Tensor:
     """A cached uint8 device buffer of at least ``nbytes`` per (device,
-    stream); calls on one stream are ordered, so reuse is safe."""
+    stream); calls on one stream are ordered, so reuse is safe.  A smaller
+    one is given back before a larger one is taken."""
     key = (torch.device(device).index, torch.cuda.current_stream(device).cuda_stream)
     buf = _WS.get(key)
     if buf is None or buf.numel() < nbytes:
+        buf = None
+        _WS.pop(key, None)
         buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
         _WS[key] = buf
     return buf

@@ -720,6 +720,11 @@ __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArg
     for (int i = lane; i < kCP; i += 64) sC[3 * kCP + i] = static_cast<__bf16>(0.0f);
     if (threadIdx.x < kH) sB2[threadIdx.x] = a0.b2[threadIdx.x];
     const float b3[3] = {a0.b3[0], a0.b3[1], a0.b3[2]};
+    // |dL/dz2| stays below 2^120 where the sum of a sample's |dL/dz3| is below this
+    float dz3_most = 0.0f;
+    #pragma unroll
+    for (int u = 0; u < 3 * kH / 64; ++u) dz3_most += fabsf(a0.w3[64 * u + lane]);
+    dz3_most = 0x1p120f / wave_total(dz3_most);   // (an infinite or NaN weight: every block is mixed)
     __syncthreads();
     const int xrow = t >> 2, xq = t & 3;   // the x' row and first column group this thread stages
     // A block's samples by a scalar base and a 32-bit lane offset (the last
@@ -957,6 +962,9 @@ __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArg
         // ---- dz3 (lane half 0), dW3 over the block's samples, dz2 = (W3^T bf16(dz3)) * relu'(z2)
         // (lane half h takes the sample of column tile h; the operand of both
         // tiles is in lane half 0)
+        // (mixed: h2 or dL/dz2 may be infinite or NaN, of which dW3's and db2's
+        // products would leave NaN in each other's columns of dX: 0 x inf)
+        bool mixed;
         bf16x8 dzb[2] = {zero8, zero8}, h2t[4];
         #pragma unroll
         for (int st = 0; st < 4; ++st) h2t[st] = tr_unit(trZ + q * (4 * 16 * kH * 2), st);   // the half's own samples
@@ -971,22 +979,35 @@ __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArg
             }
             const float g[3] = {h ? dc[1].x : dc[0].x, h ? dc[1].y : dc[0].y, h ? dc[1].z : dc[0].z};
             const float on = 32 * h + col0 <= last ? 1.0f : 0.0f;
+            float size = 0.0f;
             #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
                 const float cv = 1.0f / (1.0f + expf(-z[ch]));
                 const float dz3 = on > 0.0f ? g[ch] * cv * (1.0f - cv) : 0.0f;
                 db3[ch] += dz3;
+                size += fabsf(dz3);
                 const __bf16 b = static_cast<__bf16>(dz3);
                 sC[ch * kCP + 32 * h + m] = b;
                 const uint32_t own = __builtin_bit_cast(uint16_t, b), other = __shfl_xor(own, 32, 64);
                 dzb[0][ch] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(h ? 0u : own));
                 dzb[1][ch] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(h ? 0u : other));
             }
+            mixed = __any(!(fabsf(z[0]) + fabsf(z[1]) + fabsf(z[2]) < INFINITY && size < dz3_most));
         }
-        #pragma unroll
-        for (int st = 0; st < 4; ++st)
-            dX = mma_bf16(h2t[st], *reinterpret_cast<const bf16x8*>(sC + (m < 3 ? m : 3) * kCP + 16 * st + 8 * h),
-                          dX);
+        const int qx = mixed ? -1 : q;
+        auto dz3_col = [&](int st) {
+            return *reinterpret_cast<const bf16x8*>(sC + (m < 3 ? m : 3) * kCP + 16 * st + 8 * h);
+        };
+        if (__builtin_expect(mixed, 0)) {
+            f32x16 d = zero_tile();
+            #pragma unroll
+            for (int st = 0; st < 4; ++st) d = mma_bf16(h2t[st], dz3_col(st), d);
+            #pragma unroll
+            for (int i = 0; i < 16; ++i) dX[i] += m < 3 ? d[i] : 0.0f;
+        } else {
+            #pragma unroll
+            for (int st = 0; st < 4; ++st) dX = mma_bf16(h2t[st], dz3_col(st), dX);
+        }
         #pragma unroll
         for (int c = 0; c < 2; ++c) {
             f32x16 dh = zero_tile();
@@ -1033,8 +1054,15 @@ __global__ __launch_bounds__(512, 2) void mlp_bwd_bf16_kernel(MlpArgs a0, PosArg
                 if (st + kAhead < 8) rd(st + kAhead);
                 #pragma unroll
                 for (int c = 0; c < 2; ++c) dW2[c] = mma_bf16(A[st % (kAhead + 1)], B[st % (kAhead + 1)][c], dW2[c]);
-                if (st >> 2 == q) dX = mma_bf16(A[st % (kAhead + 1)], one3, dX);
+                if (st >> 2 == qx) dX = mma_bf16(A[st % (kAhead + 1)], one3, dX);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if (__builtin_expect(mixed, 0)) {
+                f32x16 d = zero_tile();
+                #pragma unroll
+                for (int st = 0; st < 4; ++st) d = mma_bf16(tr_unit(trZ + q * (4 * 16 * kH * 2), st), one3, d);
+                #pragma unroll
+                for (int i = 0; i < 16; ++i) dX[i] += m == 3 ? d[i] : 0.0f;
             }
         }
         __syncthreads();   // dz1 rows and dL/dfeat shares complete

@@ -11,16 +11,19 @@
 // duration: 2.7 times the rate, and 48 roundings of an accumulator over a
 // 128-wide layer instead of 64.
 //
-// Range: below about 2^-110 the low plane loses bits to underflow (an error of
-// less than 2^-130).  Above the largest bfloat16 the high plane is infinite and
-// the others are not numbers, so such an operand, or an infinity, makes every
-// sum that it enters NaN.  The forward lets a NaN through its ReLUs, and a
-// sample whose logits are not finite is evaluated by the plain float32 chain
-// instead (plain_sample).  The adjoint's operands are h1 and the inputs, which
-// the forward has checked in this way, and gradients: with dL/dc below 2^64 and
-// weights below 2^20 those stay below 2^112.  Where either is not so, or a
-// sample's logits were not finite, the adjoint takes the plain chain for every
-// sample (plain_adjoint).
+// Range: a plane below 2^-126, the smallest normal bfloat16, can count as zero,
+// so operands below about 2^-109 err by up to 2^-126 (float32 holds those down
+// to 2^-149: gradients of samples that hardly any light reaches).  Scaling the
+// gradients up would move that limit at the expense of the other one: a weight
+// gradient of the largest float32 features would overflow.  Above the largest
+// bfloat16 the high plane is infinite and the others are not numbers, so such an
+// operand, or an infinity, makes every sum that it enters NaN.  The forward lets
+// a NaN through its ReLUs, and a sample whose logits are not finite is evaluated
+// by the plain float32 chain instead (plain_sample).  The adjoint's operands are
+// h1 and the inputs, which the forward has checked in this way, and gradients:
+// with dL/dc below 2^64 and weights below 2^20 those stay below 2^112.  Where
+// either is not so, or a sample's logits were not finite, the adjoint takes the
+// plain chain for every sample (plain_adjoint).
 #pragma once
 
 #include <type_traits>

@@ -6,11 +6,12 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def test_growth_holds_one_buffer(gpu_lib):
+def test_growth_holds_one_buffer(gpu_lib, monkeypatch):
     import torch
     from paper_2111_11215_amd import api
     first, second = 64 << 20, 80 << 20
-    with torch.cuda.stream(torch.cuda.Stream()):   # a stream, and so a workspace, of its own
+    monkeypatch.setattr(api, "_WS", {})   # (a stream of the pool may have a workspace already)
+    with torch.cuda.stream(torch.cuda.Stream()):
         torch.cuda.synchronize()
         base = torch.cuda.memory_allocated()
         torch.cuda.reset_peak_memory_stats()
